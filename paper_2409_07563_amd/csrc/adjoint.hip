@@ -542,7 +542,7 @@ __global__ __launch_bounds__(kWave) void adjoint_tp_kernel(
       float res[N];
       if constexpr (BF) mlp::residual_keep<MT>(WFB, x, v, g, n, res, a1, a2);
       else mlp::residual_keep<MT>(WF, x, v, g, n, res, a1, a2);
-      step<Model, kRK4>(x, v, comp, p, res);
+      residual_step<FAST, kRK4>(x, v, comp, p, res);
     } else {
       step<Model, kRK4>(x, v, comp, p);
     }
@@ -594,7 +594,7 @@ __global__ __launch_bounds__(kWave) void adjoint_tp_kernel(
       }
 #pragma unroll
       for (int i = 0; i < N; ++i) xn[i] += p.dt * gd[i];
-      step<Model, kRK4>(x, v, comp, p, res);
+      residual_step<FAST, kRK4>(x, v, comp, p, res);
     } else {
       step<Model, kRK4>(x, v, comp, p);
     }
@@ -640,7 +640,6 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_tp_split_kernel(
     mlp::f4* __restrict__ pre) {
   static_assert(MT % SW == 0, "tiles per wave");
   constexpr int TW = MT / SW;
-  using Model = Bicycle<FAST>;
   using f4 = mlp::f4;
   using PK = mlp::Pack<MT>;
   constexpr int N = 5, M = 2;
@@ -844,7 +843,7 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_tp_split_kernel(
       for (int i = 0; i < N; ++i) xn[i] += p.dt * gd[i];
     }
     par ^= 1;
-    step<Model, kRK4>(x, v, comp, p, res);
+    residual_step<FAST, kRK4>(x, v, comp, p, res);
     if (tan) {
       const float* r = p.ref + static_cast<int64_t>(t + 1) * N;
 #pragma unroll
@@ -1039,7 +1038,7 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
             ps[t2 * kWave] = a1[t2];
             ps[(MT + t2) * kWave] = a2[t2];
           }
-          step<Model, kRK4>(x, v, comp, p, res);
+          residual_step<FAST, kRK4>(x, v, comp, p, res);
         } else {
           step<Model, kRK4>(x, v, comp, p);
         }
@@ -1233,7 +1232,6 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
     mlp::f4* __restrict__ pre, const float* __restrict__ tp, int tp_tiles) {
   static_assert(MT % SW == 0, "tiles per wave");
   constexpr int TW = MT / SW;
-  using Model = Bicycle<FAST>;
   using f4 = mlp::f4;
   using PK = mlp::Pack<MT>;
   constexpr int N = 5, M = 2, H = 16 * MT, PS = SplitLds<MT, SW>::P;
@@ -1442,7 +1440,7 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
         par ^= 1;
         float res[N];
         mlp::broadcast5(out, n, res);
-        step<Model, kRK4>(x, v, comp, p, res);
+        residual_step<FAST, kRK4>(x, v, comp, p, res);
       }
       if (w == 0 && g == 0) {
   #pragma unroll

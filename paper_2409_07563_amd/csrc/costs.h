@@ -21,15 +21,29 @@ struct CostQuadratic {
   __device__ __forceinline__ static void init(State&, const float*, const DevParams&,
                                               const float4*) {}
   template <int N, int M>
-  __device__ __forceinline__ static float running(const float* x, const float* comp, const float* v, int,
+  __device__ __forceinline__ static float running(const float* x, const float* comp, const float* v, int t,
                                                   const DevParams& p, const float4* lds, State&,
                                                   bool& hit) {
+    float r[N];
+    fetch<N>(p, t, r);
+    hit = false;
+    return running_at<N, M>(x, v, r, p);
+  }
+  // the reference of step t (here the goal), and the running cost against a
+  // reference already fetched
+  template <int N>
+  __device__ __forceinline__ static void fetch(const DevParams& p, int, float* r) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = p.ref[i];
+  }
+  template <int N, int M>
+  __device__ __forceinline__ static float running_at(const float* x, const float* v, const float* r,
+                                                     const DevParams& p) {
     float c = 0.0f;
 #pragma unroll
-    for (int i = 0; i < N; ++i) { const float e = x[i] - p.ref[i]; c += p.w[i] * e * e; }
+    for (int i = 0; i < N; ++i) { const float e = x[i] - r[i]; c += p.w[i] * e * e; }
 #pragma unroll
     for (int j = 0; j < M; ++j) c += p.w[8 + j] * v[j] * v[j];
-    hit = false;
     return c;
   }
   template <int N>
@@ -236,14 +250,24 @@ struct CostTrack {
   __device__ __forceinline__ static float running(const float* x, const float* comp, const float* v, int t,
                                                   const DevParams& p, const float4* lds, State&,
                                                   bool& hit) {
-    const float* r = p.ref + static_cast<int64_t>(t + 1) * N;
-    float c = 0.0f;
-#pragma unroll
-    for (int i = 0; i < N; ++i) { const float e = x[i] - r[i]; c += p.w[i] * e * e; }
-#pragma unroll
-    for (int j = 0; j < M; ++j) c += p.w[8 + j] * v[j] * v[j];
+    float r[N];
+    fetch<N>(p, t, r);
     hit = false;
-    return c;
+    return running_at<N, M>(x, v, r, p);
+  }
+  // the reference of step t, for kernels that request it a step ahead: waiting
+  // for a load also waits for every older one, so a reference requested at its
+  // use drains the noise requested for the steps to come
+  template <int N>
+  __device__ __forceinline__ static void fetch(const DevParams& p, int t, float* r) {
+    const float* row = p.ref + static_cast<int64_t>(t + 1) * N;
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = row[i];
+  }
+  template <int N, int M>
+  __device__ __forceinline__ static float running_at(const float* x, const float* v, const float* r,
+                                                     const DevParams& p) {
+    return CostQuadratic::running_at<N, M>(x, v, r, p);
   }
   // the terminal reference row is read by the kernel through t = T - 1
   template <int N>

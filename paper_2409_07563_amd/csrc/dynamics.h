@@ -100,11 +100,9 @@ __device__ __forceinline__ void advance(float* x, const float* x0, const float* 
   }
 }
 
-// One step.  res (optional): a residual r added as dt * r to the increment
-// (the MLP residual dynamics evaluate it on the pre-step state).
+// One step.
 template <class Model, int INTEG>
-__device__ __forceinline__ void step(float* x, const float* v, float* comp, const DevParams& p,
-                                     const float* res = nullptr) {
+__device__ __forceinline__ void step(float* x, const float* v, float* comp, const DevParams& p) {
   constexpr int N = Model::N;
   float x0[N], inc[N];
 #pragma unroll
@@ -129,12 +127,163 @@ __device__ __forceinline__ void step(float* x, const float* v, float* comp, cons
 #pragma unroll
     for (int i = 0; i < N; ++i) inc[i] = p.sixth_dt * (acc[i] + k[i]);
   }
-  if (res) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) inc[i] += p.dt * res[i];
-  }
   advance<Model>(x, x0, inc, comp);
   Model::post_step(x, p);
+}
+
+// The bicycle with a residual, x' = F(x, v) + dt g(x, v), in two parts that
+// different waves may evaluate: bicycle_increment gives what the residual is
+// added to, add_residual the new state.  Every operation is spelled out (no
+// contraction is left to the compiler), so the parts round the same wherever
+// they run.
+//   q[0..2]  the increment of position and yaw (rounded)
+//   q[3..4]  speed and steer: the increment before its last factor, inc_scale
+template <bool FAST>
+__device__ __forceinline__ float bicycle_tan(float d) {
+  if constexpr (FAST) {
+    return __sinf(d) * __builtin_amdgcn_rcpf(__cosf(d));
+  } else {
+    return tanf(d);
+  }
+}
+template <bool FAST>
+__device__ __forceinline__ void bicycle_sincos(float a, float& s, float& c) {
+  if constexpr (FAST) {
+    s = __sinf(a);
+    c = __cosf(a);
+  } else {
+    sincosf(a, &s, &c);
+  }
+}
+template <int INTEG>
+__device__ __forceinline__ float inc_scale(const DevParams& p) {
+  return INTEG == kEuler ? p.dt : p.sixth_dt;
+}
+
+template <bool FAST, int INTEG>
+__device__ __forceinline__ void bicycle_increment(const float* x, const float* v,
+                                                  const DevParams& p, float* q) {
+#pragma clang fp contract(off)
+  const float il = p.inv_wheelbase;
+  const float s1 = x[3];
+  if constexpr (INTEG == kEuler) {
+    float sn, cs;
+    bicycle_sincos<FAST>(x[2], sn, cs);
+    q[0] = p.dt * (s1 * cs);
+    q[1] = p.dt * (s1 * sn);
+    q[2] = p.dt * (s1 * bicycle_tan<FAST>(x[4]) * il);
+    q[3] = v[0];
+    q[4] = v[1];
+  } else {
+    // speed and steer are linear over the step, so stages 2 and 3 share them
+    // and their yaw rate
+    const float s2 = __builtin_fmaf(p.half_dt, v[0], s1), s4 = __builtin_fmaf(p.dt, v[0], s1);
+    const float d2 = __builtin_fmaf(p.half_dt, v[1], x[4]), d4 = __builtin_fmaf(p.dt, v[1], x[4]);
+    const float k1 = s1 * bicycle_tan<FAST>(x[4]) * il;
+    const float k2 = s2 * bicycle_tan<FAST>(d2) * il;
+    const float r4 = s4 * bicycle_tan<FAST>(d4);  // times il: the fourth stage's yaw rate
+    float sn1, cs1, sn2, cs2, sn3, cs3, sn4, cs4;
+    bicycle_sincos<FAST>(x[2], sn1, cs1);
+    bicycle_sincos<FAST>(__builtin_fmaf(p.half_dt, k1, x[2]), sn2, cs2);
+    bicycle_sincos<FAST>(__builtin_fmaf(p.half_dt, k2, x[2]), sn3, cs3);
+    bicycle_sincos<FAST>(__builtin_fmaf(p.dt, k2, x[2]), sn4, cs4);
+    auto sum4 = [&](float t1, float t2, float t3, float t4) {
+      float a = __builtin_fmaf(s1, t1, 2.0f * (s2 * t2));
+      a = __builtin_fmaf(2.0f, s2 * t3, a);
+      return __builtin_fmaf(s4, t4, a);
+    };
+    q[0] = p.sixth_dt * sum4(cs1, cs2, cs3, cs4);
+    q[1] = p.sixth_dt * sum4(sn1, sn2, sn3, sn4);
+    float a = __builtin_fmaf(2.0f, k2, k1);
+    a = __builtin_fmaf(2.0f, k2, a);
+    q[2] = p.sixth_dt * __builtin_fmaf(r4, il, a);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float b = __builtin_fmaf(2.0f, v[j], v[j]);
+      b = __builtin_fmaf(2.0f, v[j], b);
+      q[3 + j] = b + v[j];
+    }
+  }
+}
+
+// The values of v in the lanes n, 16 + n, 32 + n, 48 + n of the wave (n = lane
+// mod 16), in every one of them.
+__device__ __forceinline__ void rows_gather(float v, float (&out)[4]) {
+  const uint32_t b = __float_as_uint(v);
+  // the odd rows of the first operand trade places with the even rows of the second
+  const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  const auto e = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false);
+  const auto o = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);
+  out[0] = __uint_as_float(e[0]);
+  out[1] = __uint_as_float(o[0]);
+  out[2] = __uint_as_float(e[1]);
+  out[3] = __uint_as_float(o[1]);
+}
+
+// bicycle_increment of RK4 where the four 16-lane rows of a wave hold the same
+// sample in the same lane: row g takes stage g's tan, sin and cos (the stage
+// yaw rates need only speed and steer, so the stages do not wait for each
+// other), three gathers bring them together, and every row forms the same
+// increment with the operations of bicycle_increment.  mid() is called half way.
+template <bool FAST, class Mid>
+__device__ __forceinline__ void bicycle_increment_rows(const float* x, const float* v, int g,
+                                                       const DevParams& p, float* q, Mid&& mid) {
+#pragma clang fp contract(off)
+  const float il = p.inv_wheelbase;
+  const float s1 = x[3];
+  const float s2 = __builtin_fmaf(p.half_dt, v[0], s1), s4 = __builtin_fmaf(p.dt, v[0], s1);
+  const float d2 = __builtin_fmaf(p.half_dt, v[1], x[4]), d4 = __builtin_fmaf(p.dt, v[1], x[4]);
+  const float s = g == 0 ? s1 : g == 3 ? s4 : s2;
+  float r[4], cs[4], sn[4], mysn, mycs;
+  rows_gather(s * bicycle_tan<FAST>(g == 0 ? x[4] : g == 3 ? d4 : d2), r);
+  const float k1 = r[0] * il, k2 = r[1] * il;
+  mid();
+  // stage 2 leaves from x along k1, stages 3 and 4 along k2 (k3 = k2)
+  const float a1 = __builtin_fmaf(g == 3 ? p.dt : p.half_dt, g == 1 ? k1 : k2, x[2]);
+  bicycle_sincos<FAST>(g == 0 ? x[2] : a1, mysn, mycs);
+  rows_gather(mycs, cs);
+  rows_gather(mysn, sn);
+  auto sum4 = [&](const float (&t)[4]) {
+    float a = __builtin_fmaf(s1, t[0], 2.0f * (s2 * t[1]));
+    a = __builtin_fmaf(2.0f, s2 * t[2], a);
+    return __builtin_fmaf(s4, t[3], a);
+  };
+  q[0] = p.sixth_dt * sum4(cs);
+  q[1] = p.sixth_dt * sum4(sn);
+  float a = __builtin_fmaf(2.0f, k2, k1);
+  a = __builtin_fmaf(2.0f, k2, a);
+  q[2] = p.sixth_dt * __builtin_fmaf(r[3], il, a);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float b = __builtin_fmaf(2.0f, v[j], v[j]);
+    b = __builtin_fmaf(2.0f, v[j], b);
+    q[3 + j] = b + v[j];
+  }
+}
+
+template <int INTEG>
+__device__ __forceinline__ void add_residual(float* x, float* comp, const float* q,
+                                             const float* res, const DevParams& p) {
+#pragma clang fp contract(off)
+  const float h = inc_scale<INTEG>(p);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {  // compensated, as advance() does
+    const float y = __builtin_fmaf(p.dt, res[i], q[i]) - comp[i];
+    const float t = x[i] + y;
+    comp[i] = (t - x[i]) - y;
+    x[i] = t;
+  }
+  x[2] = x[2] + __builtin_fmaf(p.dt, res[2], q[2]);
+#pragma unroll
+  for (int i = 3; i < 5; ++i) x[i] = x[i] + __builtin_fmaf(h, q[i], p.dt * res[i]);
+}
+
+template <bool FAST, int INTEG>
+__device__ __forceinline__ void residual_step(float* x, const float* v, float* comp,
+                                              const DevParams& p, const float* res) {
+  float q[5];
+  bicycle_increment<FAST, INTEG>(x, v, p, q);
+  add_residual<INTEG>(x, comp, q, res, p);
 }
 
 }  // namespace mppi

@@ -427,6 +427,14 @@ __device__ __forceinline__ bf8 kblock_operand(const f4 (&h)[MT], int kb) {
   return __builtin_convertvector(v, bf8);
 }
 
+// The activations of one M-tile as half a K-block operand (the values
+// kblock_operand would round), and a whole one from its two halves.
+typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ bf4 kblock_half(f4 h) { return __builtin_convertvector(h, bf4); }
+__device__ __forceinline__ bf8 kblock_join(bf4 a, bf4 b) {
+  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // The input-layer B operand: z = (x0..x4, v0, v1) in lane group 0, rounded.
 __device__ __forceinline__ bf8 input_operand_bf(const float* x, const float* v, int g) {
   const fl8 zf = g == 0 ? fl8{x[0], x[1], x[2], x[3], x[4], v[0], v[1], 0.0f}

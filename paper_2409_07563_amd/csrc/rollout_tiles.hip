@@ -52,7 +52,13 @@ __global__ __launch_bounds__(kWave) void rollout_tile_kernel(
   float sum = 0.0f, sum_c = 0.0f;
   int next_ckpt = 0;
   float* ck = ckpt ? ckpt + k : nullptr;
+  float rn[N];  // the reference of the coming step
+  Cost::template fetch<N>(p, 0, rn);
   noise_steps<M, 8>(e, ldk, T, [&](int t, const float* nz, int) {
+    float r[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = rn[i];
+    Cost::template fetch<N>(p, min(t + 1, T - 1), rn);
     float v[M];
 #pragma unroll
     for (int j = 0; j < M; ++j) v[j] = mean * lds_u[t * M + j] + nz[j];
@@ -69,12 +75,11 @@ __global__ __launch_bounds__(kWave) void rollout_tile_kernel(
     if constexpr (MT > 0) {
       float res[N];
       mlp::residual<MT>(W, x, v, g, n, res);
-      step<Model, INTEG>(x, v, comp, p, res);
+      residual_step<FAST, INTEG>(x, v, comp, p, res);
     } else {
       step<Model, INTEG>(x, v, comp, p);
     }
-    bool hit;
-    float l = Cost::template running<N, M>(x, comp, v, t, p, lds, cs, hit);
+    float l = Cost::template running_at<N, M>(x, v, r, p);
     if (p.importance && plain) l += is_term<M>(p, t, v, lds_u + t * M);
     if (p.cosines) l += inflation(p);
     const float y = l - sum_c;
@@ -86,43 +91,69 @@ __global__ __launch_bounds__(kWave) void rollout_tile_kernel(
   if (g == 0 && live) S[k] = __builtin_isfinite(sum) ? sum : __builtin_inff();
 }
 
-// The same rollout with the MLP split over SW waves of one workgroup (SW = 2
-// or 4, H = 16 MT hidden units): wave w owns the MT / SW M-tiles q = w MT/SW
-// ... of both hidden layers and the same K-tiles of the output layer.  Per
-// step the waves exchange their h1 tiles and their per-K-tile output partials
-// through LDS (double-buffered by step parity, two barriers).  Every
-// per-element accumulation runs in the same order as in the one-wave kernel
-// (layer 2: K-steps (tt, i) in order; output: the K-tile partials summed 0,
-// 1, ..., MT-1), so the results are bitwise the same.  One leader wave per
-// tile (wave blockIdx mod SW, so that the leaders of the tiles spread over
-// the SIMDs) takes the bicycle step and the running cost and hands the new
-// state to the other waves through LDS at a third barrier: the step's VALU
-// work is done once per tile instead of SW times.  More waves keep more
-// SIMDs busy, and a wave's matrix-core work overlaps another wave's VALU
-// work.
-// BF (the bfloat16 products of mlp::hidden_bf / output_bf): the waves
-// exchange their h2 tiles instead of output partials, and the leader forms
-// the output over every K-block in order, so each product is the one-wave
-// kernel's and the results are bitwise the same as there too.
+// The same rollout with a tile's work divided over the waves of one workgroup
+// (H = 16 MT hidden units, SW = 2 or 4).  The step x' = F(x, v) + dt g(x, v)
+// evaluates both terms at the state before the step, so they run side by side:
+//   MLP wave w (SW of them) takes the M-tiles w MT/SW .. of both hidden layers
+//   and the same K-tiles of the output layer;
+//   the bicycle wave forms the RK4 (or Euler) increment;
+//   the cost wave charges the step before: running cost, checkpoint, sum.
+// Per step:
+//   the MLP waves write their h1 tiles to LDS;                        barrier
+//   the MLP waves take layer 2 over all of h1 and write their output
+//   partials (BF: their h2 tiles), the bicycle wave its increment;    barrier
+//   every wave adds the two and has the new state.
+// A step is one dependent chain (the matrix cores' accumulations, the
+// activations, two exchanges), and at K = 8192 a CU holds two tiles, so the
+// length of the chain and the busiest SIMD bound the kernel: a binary32 MFMA
+// keeps its SIMD's vector unit from issuing, and the bicycle's and the cost's
+// arithmetic must not pile up on one SIMD.  Eight waves are launched for SW = 4
+// (two per SIMD), of which two stay besides the MLP's four; which two depends on
+// the workgroup, so that the helper waves of the two workgroups of a CU sit on
+// four different SIMDs.
+// K = 8192, T = 100, us, against a form that repeated the bicycle step after the
+// MLP and handed the state back through a third barrier: H = 64 175 -> 137 (one
+// tile per CU, K = 4096: 126 -> 84), BF 111 -> 89; H = 32 140 -> 90, BF 98 -> 69.
+// The matrix cores alone take 59 us at H = 64, and a binary32 MFMA and the vector
+// unit of a SIMD do not overlap (measured), which leaves about 100 us as the
+// floor of this arithmetic.
+//
+// The lanes of a wave hold the state as the next layer consumes it: lane group
+// g needs x_g and (group 0) x_4, so the output layer's rows are laid out to give
+// group g output g in accumulator register 0 and output 4 in register 1 (a lane
+// reads another lane's row of the weight pack; the products are the same), and
+// no value crosses lane groups.  In BF the input operand wants the whole state
+// in lane group 0, so every MLP wave forms all outputs (over every K-block in
+// order) and one v_permlane16_swap brings output 4 from group 1 to group 0.
+//
+// Every accumulation runs in the one-wave kernel's order and the increment and
+// the step's last additions round as there (bicycle_increment, add_residual),
+// so the results are bitwise the same (tested).  Each role runs its own step
+// loop with the same two barriers per step; the role is a scalar, so a wave
+// only ever meets its own role's barriers, T times two of them.
+constexpr int split_launch_waves(int SW) { return SW == 4 ? 8 : SW + 2; }
+
 template <int MT, int SW, int INTEG, class Cost, bool FAST, bool BF = false>
-__global__ __launch_bounds__(kWave * SW) void rollout_tile_split_kernel(
+__global__ __launch_bounds__(kWave * split_launch_waves(SW)) void rollout_tile_split_kernel(
     DevParams p, const float* __restrict__ x0, const float* __restrict__ u,
     const float* __restrict__ eps, int64_t ldk, int K, int T, float* __restrict__ S,
     float* __restrict__ ckpt, int ckpt_every) {
-  static_assert(MT % SW == 0, "tiles per wave");
+  static_assert(MT % SW == 0 && MT % 2 == 0, "tiles per wave, whole K-blocks");
   constexpr int TW = MT / SW;  // M-tiles per wave
-  using Model = Bicycle<FAST>;
+  constexpr int N = 5, M = 2;
+  constexpr int kOut = 12;  // floats per sample of an output partial (16-byte rows, no bank conflicts)
   using f4 = mlp::f4;
   using P = mlp::Pack<MT>;
-  constexpr int N = Model::N, M = Model::M;
-  __shared__ f4 xh[2][MT][kWave];  // h1 tiles
-  __shared__ f4 xg[2][MT][kWave];  // output partials per K-tile (BF: h2 tiles)
-  __shared__ float xs[kTile][8];   // the leader's new state of the tile's samples
+  using tile_t = std::conditional_t<BF, mlp::bf4, f4>;  // BF: rounded by the wave that formed it
+  __shared__ tile_t xh[MT][kWave];           // h1 tiles
+  __shared__ tile_t xg[BF ? MT : 1][kWave];  // BF: h2 tiles
+  __shared__ float xo[BF ? 1 : MT][kTile][kOut];  // output partials 0..4 per K-tile
+  __shared__ float xq[kTile][8];             // the bicycle's increment
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * M, lds);
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
+  const int lane = threadIdx.x % kWave;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n = lane % kTile, g = lane / kTile;
-  const bool leader = w == static_cast<int>(blockIdx.x % SW);
   const int k = blockIdx.x * kTile + n;
   const bool live = k < K;
   const bool plain = k < p.n_plain;  // drawn around u (else around zero)
@@ -130,28 +161,183 @@ __global__ __launch_bounds__(kWave * SW) void rollout_tile_split_kernel(
   // exactly u + eps for mean = 1), no branch around the load of u
   const float mean = plain ? 1.0f : 0.0f;
   const float* e = eps + (live ? k : K - 1);
-  // this wave's operands (tiles q0 .. q0 + TW - 1)
+
+  if (w >= SW) {  // a helper wave
+    constexpr int kCus = 256;
+    const int turn = SW == 4 ? (blockIdx.x / kCus) & 1 : 0;
+    const int bicycle = SW + turn, cost = SW + turn + (SW == 4 ? 2 : 1);
+    if (w != bicycle && w != cost) return;
+    float x[N], comp[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) { x[i] = x0[i]; comp[i] = 0.0f; }
+    mlp::WeightsBf<MT> WB;  // BF: the output rows
+    if constexpr (BF) WB.load(p.mlp_bf, p.mlp, lane);
+    // the state after the step, from the MLP's outputs and the increment q
+    auto finish = [&](const float* q) {
+      float res[N];
+      if constexpr (BF) {
+        f4 o = WB.b3();
+#pragma unroll
+        for (int kb = 0; kb < mlp::PackBf<MT>::KB; ++kb)
+          o = mlp::mfma_bf(WB.w3(kb), mlp::kblock_join(xg[2 * kb][lane], xg[2 * kb + 1][lane]), o);
+        mlp::broadcast5(o, n, res);
+      } else {
+        f4 o = *reinterpret_cast<const f4*>(&xo[0][n][0]);
+        res[4] = xo[0][n][4];
+#pragma unroll
+        for (int tt = 1; tt < MT; ++tt) {
+          o += *reinterpret_cast<const f4*>(&xo[tt][n][0]);
+          res[4] += xo[tt][n][4];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) res[i] = o[i];
+      }
+      add_residual<INTEG>(x, comp, q, res, p);
+    };
+    if (w == bicycle) {
+      noise_steps<M, 8>(e, ldk, T, [&](int t, const float* nz, int) {
+        float v[M], q[N];
+#pragma unroll
+        for (int j = 0; j < M; ++j) v[j] = mean * lds_u[t * M + j] + nz[j];
+        if constexpr (INTEG == kRK4) {
+          bicycle_increment_rows<FAST>(x, v, g, p, q, [] { __syncthreads(); });
+        } else {
+          __syncthreads();
+          bicycle_increment<FAST, INTEG>(x, v, p, q);
+        }
+        if (g == 0) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) xq[n][i] = q[i];
+        }
+        __syncthreads();
+        finish(q);
+      });
+      return;
+    }
+    typename Cost::State cs;
+    Cost::init(cs, x, p, lds);
+    float sum = 0.0f, sum_c = 0.0f;
+    int next_ckpt = 0;
+    float* ck = ckpt ? ckpt + k : nullptr;
+    float vp[M] = {0.0f, 0.0f};  // the control of the step before
+    float rn[N];                 // the reference of the step to be charged next
+    Cost::template fetch<N>(p, 0, rn);
+    auto charge = [&](int t) {   // the running cost of step t at x_{t+1}
+      float l = Cost::template running_at<N, M>(x, vp, rn, p);
+      Cost::template fetch<N>(p, min(t + 1, T - 1), rn);
+      if (p.importance && plain) l += is_term<M>(p, t, vp, lds_u + t * M);
+      if (p.cosines) l += inflation(p);
+      const float y = l - sum_c;
+      const float s = sum + y;
+      sum_c = (s - sum) - y;
+      sum = s;
+    };
+    noise_steps<M, 8>(e, ldk, T, [&](int t, const float* nz, int) {
+      if (t > 0) charge(t - 1);
+      __syncthreads();
+      if (ck && t == next_ckpt) {
+        if (g == 0 && live) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) ck[i * ldk] = x[i];
+          ck[5 * ldk] = comp[0];
+          ck[6 * ldk] = comp[1];
+        }
+        ck += kCkptWords * ldk;
+        next_ckpt += ckpt_every;
+      }
+#pragma unroll
+      for (int j = 0; j < M; ++j) vp[j] = mean * lds_u[t * M + j] + nz[j];
+      __syncthreads();
+      float q[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) q[i] = xq[n][i];
+      finish(q);
+    });
+    charge(T - 1);
+    sum = sum + (terminal_cost<Cost, N>(x, T, p, lds, cs) - sum_c);
+    if (g == 0 && live) S[k] = __builtin_isfinite(sum) ? sum : __builtin_inff();
+    return;
+  }
+
+  // an MLP wave: its operands (tiles q0 .. q0 + TW - 1)
   const int q0 = w * TW;
   const float* pk = p.mlp + lane;
   auto at = [&](int row) { return pk[row * kWave]; };
-  // binary32 operands (unused in BF), and the bfloat16 ones (unused otherwise)
-  constexpr int KB = mlp::PackBf<MT>::KB;
-  constexpr int TWF = BF ? 1 : TW, MTF = BF ? 1 : MT;
-  constexpr int TWB = BF ? TW : 1, KBB = BF ? KB : 1;
-  float w1[TWF][2], w2[TWF][MTF][4], w3[TWF][4];
-  mlp::bf8 v1[TWB], v2[TWB][KBB], v3[KBB];
-  f4 b1[TW], b2[TW], b3[TW];
+  f4 b1[TW], b2[TW];
 #pragma unroll
-  for (int q = 0; q < TW; ++q) {
-    const int t = q0 + q;
-    if constexpr (BF) {
-      using PB = mlp::PackBf<MT>;
+  for (int q = 0; q < TW; ++q)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      b1[q][i] = at(P::kB1 + 4 * (q0 + q) + i);
+      b2[q][i] = at(P::kB2 + 4 * (q0 + q) + i);
+    }
+  if constexpr (BF) {
+    using PB = mlp::PackBf<MT>;
+    constexpr int KB = PB::KB;
+    mlp::WeightsBf<MT> W;  // the output rows; the own tiles' rows below
+    W.load(p.mlp_bf, p.mlp, lane);
+    mlp::bf8 v1[TW], v2[TW][KB];
+#pragma unroll
+    for (int q = 0; q < TW; ++q) {
       const uint4* bp = p.mlp_bf + lane;
-      v1[q] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW1 + t) * kWave]);
+      v1[q] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW1 + q0 + q) * kWave]);
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
-        v2[q][kb] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW2 + t * KB + kb) * kWave]);
-    } else {
+        v2[q][kb] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW2 + (q0 + q) * KB + kb) * kWave]);
+    }
+    // lane group 0 carries the state (the others' copies are never used)
+    float x[N], comp[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) { x[i] = x0[i]; comp[i] = 0.0f; }
+    float un[M] = {lds_u[0], lds_u[1]};  // u of the coming step, read a step ahead
+    noise_steps<M, 8>(e, ldk, T, [&](int t, const float* nz, int) {
+      float v[M];
+#pragma unroll
+      for (int j = 0; j < M; ++j) v[j] = mean * un[j] + nz[j];
+      const mlp::bf8 zb = mlp::input_operand_bf(x, v, g);
+#pragma unroll
+      for (int q = 0; q < TW; ++q)
+        xh[q0 + q][lane] = mlp::kblock_half(mlp::tanh4(mlp::mfma_bf(v1[q], zb, b1[q])));
+      __syncthreads();
+      mlp::bf8 hb[KB];
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+        hb[kb] = mlp::kblock_join(xh[2 * kb][lane], xh[2 * kb + 1][lane]);
+      const int t1 = min(t + 1, T - 1);
+#pragma unroll
+      for (int j = 0; j < M; ++j) un[j] = lds_u[t1 * M + j];
+      f4 acc[TW];
+#pragma unroll
+      for (int q = 0; q < TW; ++q) {
+        acc[q] = b2[q];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) acc[q] = mlp::mfma_bf(v2[q][kb], hb[kb], acc[q]);
+        xg[q0 + q][lane] = mlp::kblock_half(mlp::tanh4(acc[q]));
+      }
+      __syncthreads();
+      float qi[N], res[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) qi[i] = xq[n][i];
+      f4 o = W.b3();
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+        o = mlp::mfma_bf(W.w3(kb), mlp::kblock_join(xg[2 * kb][lane], xg[2 * kb + 1][lane]), o);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) res[i] = o[i];
+      const uint32_t o0 = __float_as_uint(o[0]);
+      res[4] = __uint_as_float(__builtin_amdgcn_permlane16_swap(o0, o0, false, false)[1]);
+      add_residual<INTEG>(x, comp, qi, res, p);
+    });
+  } else {
+    float w1[TW][2], w2[TW][MT][4], w3[TW][4];
+    f4 b3[TW];
+    // output row m of the accumulator takes output m / 4 (m = 0 mod 4), output
+    // 4 (m = 1 mod 4) or the pack's padding row
+    const int m3 = (n & 3) == 0 ? n / 4 : (n & 3) == 1 ? 4 : 15;
+    const float* pk3 = p.mlp + kTile * g + m3;
+#pragma unroll
+    for (int q = 0; q < TW; ++q) {
+      const int t = q0 + q;
       w1[q][0] = at(P::kW1 + 2 * t);
       w1[q][1] = at(P::kW1 + 2 * t + 1);
 #pragma unroll
@@ -159,133 +345,70 @@ __global__ __launch_bounds__(kWave * SW) void rollout_tile_split_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) w2[q][tt][i] = at(P::kW2 + (t * MT + tt) * 4 + i);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) w3[q][i] = at(P::kW3 + 4 * t + i);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      b1[q][i] = at(P::kB1 + 4 * t + i);
-      b2[q][i] = at(P::kB2 + 4 * t + i);
-      b3[q][i] = (BF || t == 0) ? at(P::kB3 + i) : 0.0f;
-    }
-  }
-  if constexpr (BF) {
-    using PB = mlp::PackBf<MT>;
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-      v3[kb] = __builtin_bit_cast(mlp::bf8, p.mlp_bf[(PB::kW3 + kb) * kWave + lane]);
-  }
-  float x[N], comp[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) { x[i] = x0[i]; comp[i] = 0.0f; }
-  typename Cost::State cs;
-  Cost::init(cs, x, p, lds);
-  float sum = 0.0f, sum_c = 0.0f;
-  int next_ckpt = 0;
-  float* ck = ckpt ? ckpt + k : nullptr;
-  noise_steps<M, 8>(e, ldk, T, [&](int t, const float* nz, int) {
-    const int par = t & 1;
-    float v[M];
-#pragma unroll
-    for (int j = 0; j < M; ++j) v[j] = mean * lds_u[t * M + j] + nz[j];
-    if (ck && t == next_ckpt) {
-      if (leader && g == 0 && live) {  // the leader's compensation is current
-#pragma unroll
-        for (int i = 0; i < N; ++i) ck[i * ldk] = x[i];
-        ck[5 * ldk] = comp[0];
-        ck[6 * ldk] = comp[1];
+      for (int i = 0; i < 4; ++i) w3[q][i] = pk3[(P::kW3 + 4 * t + i) * kWave];
+      b3[q] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (t == 0) {
+        b3[q][0] = p.mlp[(P::kB3 + g) * kWave];       // output g
+        b3[q][1] = p.mlp[P::kB3 * kWave + kTile];     // output 4
       }
-      ck += kCkptWords * ldk;
-      next_ckpt += ckpt_every;
     }
-    // layer 1, own tiles
-    if constexpr (BF) {
-      const mlp::bf8 zb = mlp::input_operand_bf(x, v, g);
-#pragma unroll
-      for (int q = 0; q < TW; ++q) xh[par][q0 + q][lane] = mlp::tanh4(mlp::mfma_bf(v1[q], zb, b1[q]));
-    } else {
-      const float z0 = mlp::input_operand(x, v, g, 0), z1 = mlp::input_operand(x, v, g, 1);
+    // x_g (with its compensation: positions only), x_4 and the control that
+    // the lane group's input slots take
+    float xa = x0[g], xb = x0[4], ca = 0.0f;
+    const int j = g == 2 ? 1 : 0;
+    const float h = inc_scale<INTEG>(p);
+    float un = lds_u[j];  // u of the coming step, read a step ahead
+    noise_steps<1, 8>(e + j * ldk, M * ldk, T, [&](int t, const float* nz, int) {
+      const float v = mean * un + nz[0];
+      const float z1 = g == 0 ? xb : g == 3 ? 0.0f : v;
 #pragma unroll
       for (int q = 0; q < TW; ++q)
-        xh[par][q0 + q][lane] =
-            mlp::tanh4(mlp::mfma(w1[q][1], z1, mlp::mfma(w1[q][0], z0, b1[q])));
-    }
-    __syncthreads();
-    f4 h1[MT];  // every tile, the own ones included, read back from LDS
+        xh[q0 + q][lane] = mlp::tanh4(mlp::mfma(w1[q][1], z1, mlp::mfma(w1[q][0], xa, b1[q])));
+      __syncthreads();
+      // every read is requested before the first product (the compiler would
+      // fetch the later tiles in the middle of the chain)
+      f4 h1[MT], acc[TW];
 #pragma unroll
-    for (int tt = 0; tt < MT; ++tt) h1[tt] = xh[par][tt][lane];
-    // layer 2, own tiles, over all of h1
-    f4 acc[TW];
+      for (int tt = 0; tt < MT; ++tt) h1[tt] = xh[tt][lane];
+      un = lds_u[min(t + 1, T - 1) * M + j];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int q = 0; q < TW; ++q) acc[q] = b2[q];
-    if constexpr (BF) {
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const mlp::bf8 hb = mlp::kblock_operand<MT>(h1, kb);
-#pragma unroll
-        for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma_bf(v2[q][kb], hb, acc[q]);
-      }
-      // the own h2 tiles to the leader
-#pragma unroll
-      for (int q = 0; q < TW; ++q) xg[par][q0 + q][lane] = mlp::tanh4(acc[q]);
-    } else {
+      for (int q = 0; q < TW; ++q) acc[q] = b2[q];
 #pragma unroll
       for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
           for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma(w2[q][tt][i], h1[tt][i], acc[q]);
-      // output partials of the own K-tiles
 #pragma unroll
       for (int q = 0; q < TW; ++q) {
         const f4 h2 = mlp::tanh4(acc[q]);
+        __builtin_amdgcn_sched_barrier(0);  // the four activations side by side, then the products
         f4 part = b3[q];
 #pragma unroll
         for (int i = 0; i < 4; ++i) part = mlp::mfma(w3[q][i], h2[i], part);
-        xg[par][q0 + q][lane] = part;
+        xo[q0 + q][n][g] = part[0];
+        if (g == 0) xo[q0 + q][n][4] = part[1];
       }
-    }
-    __syncthreads();
-    if (leader) {  // a wave-uniform branch
-      f4 out;
-      if constexpr (BF) {
-        f4 h2[MT];
+      __syncthreads();
+      float ra = xo[0][n][g], rb = xo[0][n][4];
 #pragma unroll
-        for (int tt = 0; tt < MT; ++tt) h2[tt] = xg[par][tt][lane];
-        out = b3[0];
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) out = mlp::mfma_bf(v3[kb], mlp::kblock_operand<MT>(h2, kb), out);
-      } else {
-        out = xg[par][0][lane];
-#pragma unroll
-        for (int tt = 1; tt < MT; ++tt) out += xg[par][tt][lane];
+      for (int tt = 1; tt < MT; ++tt) {
+        ra += xo[tt][n][g];
+        rb += xo[tt][n][4];
       }
-      float res[N];
-      mlp::broadcast5(out, n, res);
-      step<Model, INTEG>(x, v, comp, p, res);
-      bool hit;
-      float l = Cost::template running<N, M>(x, comp, v, t, p, lds, cs, hit);
-      if (p.importance && plain) l += is_term<M>(p, t, v, lds_u + t * M);
-      if (p.cosines) l += inflation(p);
-      const float y = l - sum_c;
-      const float s = sum + y;
-      sum_c = (s - sum) - y;
-      sum = s;
-      if (g == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) xs[n][i] = x[i];
+      const float qa = xq[n][g], qb = xq[n][4];
+      {
+#pragma clang fp contract(off)
+        // add_residual for components g and 4
+        const float ia = g < 3 ? __builtin_fmaf(p.dt, ra, qa) : __builtin_fmaf(h, qa, p.dt * ra);
+        const float y = ia - ca;
+        const float s = xa + y;
+        ca = g < 2 ? (s - xa) - y : 0.0f;
+        xa = s;
+        xb = xb + __builtin_fmaf(h, qb, p.dt * rb);
       }
-    }
-    // the others take the new state (xs is next written after the next
-    // step's second barrier, which every wave reaches after this read)
-    __syncthreads();
-    if (!leader) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) x[i] = xs[n][i];
-    }
-  });
-  if (leader) {
-    sum = sum + (terminal_cost<Cost, N>(x, T, p, lds, cs) - sum_c);
-    if (g == 0 && live) S[k] = __builtin_isfinite(sum) ? sum : __builtin_inff();
+    });
   }
 }
 
@@ -378,8 +501,10 @@ hipError_t launch_rollout_tiles(uint32_t dynamics, uint32_t integrator, uint32_t
                                        static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>((K + kTile - 1) / kTile)), dim3(kWave * waves),
-                     lds, stream, p, d_x0, d_u, d_eps, ldk, K, T, d_S, d_ckpt, ckpt_every);
+  // the split forms' helper waves come on top of the MLP's
+  const int block = kWave * (waves > 1 ? split_launch_waves(waves) : 1);
+  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>((K + kTile - 1) / kTile)), dim3(block), lds,
+                     stream, p, d_x0, d_u, d_eps, ldk, K, T, d_S, d_ckpt, ckpt_every);
   return hipGetLastError();
 }
 
