@@ -184,79 +184,92 @@ __global__ __launch_bounds__(kProjectSamples) void adjoint_compact_kernel(
   list[offs[blockIdx.x] + rank] = BwdItem{k, a};
 }
 
-// dx += (df/dx)^T c, dL += (df/d wheelbase)^T c and dv += (df/dv)^T c for
-// the bicycle derivative f = (s cos psi, s sin psi, s tan(delta) / L, a,
-// delta_rate) at x with control v = (a, delta_rate).
+// What the transpose of an RK4 bicycle step needs of its four stages: the
+// speed, the sine and cosine of the yaw and the tangent of the steer.  Stages 2
+// and 3 share speed and steer.
+struct BicycleStages {
+  float s[4], sn[4], cs[4], tn[4];
+};
+
 template <bool FAST>
-__device__ __forceinline__ void bicycle_vjp(const float* x, const float* c, float inv_l,
-                                            float* dx, float& dl, float* dv) {
-  dv[0] += c[3];
-  dv[1] += c[4];
-  float sn, cs, sd, cd;
-  if constexpr (FAST) {
-    sn = __sinf(x[2]);
-    cs = __cosf(x[2]);
-    sd = __sinf(x[4]);
-    cd = __cosf(x[4]);
-  } else {
-    sincosf(x[2], &sn, &cs);
-    sincosf(x[4], &sd, &cd);
-  }
-  const float rc = FAST ? __builtin_amdgcn_rcpf(cd) : 1.0f / cd;
-  const float tn = FAST ? sd * rc : tanf(x[4]);
-  const float s = x[3];
-  dx[2] += s * (cs * c[1] - sn * c[0]);
-  dx[3] += cs * c[0] + sn * c[1] + tn * inv_l * c[2];
-  dx[4] += s * (1.0f + tn * tn) * inv_l * c[2];
-  dl -= s * tn * inv_l * inv_l * c[2];
+__device__ __forceinline__ void bicycle_stages(const DevParams& p, const float* x, const float* v,
+                                               BicycleStages& st) {
+#pragma clang fp contract(off)
+  st.s[0] = x[3];
+  st.s[1] = st.s[2] = __builtin_fmaf(p.half_dt, v[0], x[3]);
+  st.s[3] = __builtin_fmaf(p.dt, v[0], x[3]);
+  st.tn[0] = bicycle_tan<FAST>(x[4]);
+  st.tn[1] = st.tn[2] = bicycle_tan<FAST>(__builtin_fmaf(p.half_dt, v[1], x[4]));
+  st.tn[3] = bicycle_tan<FAST>(__builtin_fmaf(p.dt, v[1], x[4]));
+  const float k1 = st.s[0] * st.tn[0] * p.inv_wheelbase;
+  const float k2 = st.s[1] * st.tn[1] * p.inv_wheelbase;
+  bicycle_sincos<FAST>(x[2], st.sn[0], st.cs[0]);
+  bicycle_sincos<FAST>(__builtin_fmaf(p.half_dt, k1, x[2]), st.sn[1], st.cs[1]);
+  bicycle_sincos<FAST>(__builtin_fmaf(p.half_dt, k2, x[2]), st.sn[2], st.cs[2]);
+  bicycle_sincos<FAST>(__builtin_fmaf(p.dt, k2, x[2]), st.sn[3], st.cs[3]);
 }
 
-// mu0 = (dF/dx)^T mu for the RK4 bicycle step from x (control v held),
-// gL += (dF/d wheelbase)^T mu and dv += (dF/dv)^T mu: the four stages are
-// rebuilt, then transposed in reverse.
+// The same where the wave's four 16-lane rows hold the same sample (row g takes
+// stage g; see bicycle_increment_rows), with the same operations.
 template <bool FAST>
-__device__ __forceinline__ void rk4_vjp(const DevParams& p, const float* xt, const float* v,
+__device__ __forceinline__ void bicycle_stages_rows(const DevParams& p, const float* x,
+                                                    const float* v, int g, BicycleStages& st) {
+#pragma clang fp contract(off)
+  st.s[0] = x[3];
+  st.s[1] = st.s[2] = __builtin_fmaf(p.half_dt, v[0], x[3]);
+  st.s[3] = __builtin_fmaf(p.dt, v[0], x[3]);
+  const float d2 = __builtin_fmaf(p.half_dt, v[1], x[4]), d4 = __builtin_fmaf(p.dt, v[1], x[4]);
+  rows_gather(bicycle_tan<FAST>(g == 0 ? x[4] : g == 3 ? d4 : d2), st.tn);
+  const float k1 = st.s[0] * st.tn[0] * p.inv_wheelbase;
+  const float k2 = st.s[1] * st.tn[1] * p.inv_wheelbase;
+  const float a1 = __builtin_fmaf(g == 3 ? p.dt : p.half_dt, g == 1 ? k1 : k2, x[2]);
+  float sn, cs;
+  bicycle_sincos<FAST>(g == 0 ? x[2] : a1, sn, cs);
+  rows_gather(sn, st.sn);
+  rows_gather(cs, st.cs);
+}
+
+// mu0 = (dF/dx)^T mu for the RK4 bicycle step (control held), gL +=
+// (dF/d wheelbase)^T mu and dv += (dF/dv)^T mu: the stages transposed in
+// reverse.  Stage j's cotangent c enters through f = (s cos psi, s sin psi,
+// s tan(delta) / L, a, delta_rate); nothing depends on the position.
+__device__ __forceinline__ void rk4_vjp(const DevParams& p, const BicycleStages& st,
                                         const float* mu, float* mu0, float& gL, float* dv) {
-  using Model = Bicycle<FAST>;
+#pragma clang fp contract(off)
   constexpr int N = 5;
-  float k1[N], xa[N], k2[N], xb[N], k3[N], xc[N];
-  Model::deriv(xt, v, k1, p);
+  const float il = p.inv_wheelbase, third_dt = 2.0f * p.sixth_dt;
 #pragma unroll
-  for (int i = 0; i < N; ++i) xa[i] = xt[i] + p.half_dt * k1[i];
-  Model::deriv(xa, v, k2, p);
+  for (int i = 0; i < N; ++i) mu0[i] = mu[i];
+  float cx[N] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};  // the later stage's share, components 2..4
 #pragma unroll
-  for (int i = 0; i < N; ++i) xb[i] = xt[i] + p.half_dt * k2[i];
-  Model::deriv(xb, v, k3, p);
+  for (int j = 3; j >= 0; --j) {
+    // stage j + 1 leaves from x + h k_j
+    const float wt = j == 1 || j == 2 ? third_dt : p.sixth_dt;
+    const float h = j == 2 ? p.dt : p.half_dt;
+    float c[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) xc[i] = xt[i] + p.dt * k3[i];
-  float cst[N], cx[N];
-  const float third_dt = 2.0f * p.sixth_dt;
+    for (int i = 0; i < N; ++i)
+      c[i] = (i < 2 || j == 3) ? wt * mu[i] : __builtin_fmaf(wt, mu[i], h * cx[i]);
+    const float s = st.s[j], sn = st.sn[j], cs = st.cs[j], tn = st.tn[j];
+    const float tl = tn * il;
+    cx[2] = s * __builtin_fmaf(cs, c[1], -(sn * c[0]));
+    cx[3] = __builtin_fmaf(cs, c[0], __builtin_fmaf(sn, c[1], tl * c[2]));
+    cx[4] = s * (__builtin_fmaf(tn, tn, 1.0f) * il) * c[2];
+    gL = __builtin_fmaf(-(s * tl * il), c[2], gL);
+    dv[0] += c[3];
+    dv[1] += c[4];
 #pragma unroll
-  for (int i = 0; i < N; ++i) { mu0[i] = mu[i]; cst[i] = p.sixth_dt * mu[i]; cx[i] = 0.0f; }
-  bicycle_vjp<FAST>(xc, cst, p.inv_wheelbase, cx, gL, dv);  // k4 = f(xc), xc = x + dt k3
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    mu0[i] += cx[i];
-    cst[i] = third_dt * mu[i] + p.dt * cx[i];
-    cx[i] = 0.0f;
+    for (int i = 2; i < N; ++i) mu0[i] += cx[i];
   }
-  bicycle_vjp<FAST>(xb, cst, p.inv_wheelbase, cx, gL, dv);  // k3 = f(xb), xb = x + dt/2 k2
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    mu0[i] += cx[i];
-    cst[i] = third_dt * mu[i] + p.half_dt * cx[i];
-    cx[i] = 0.0f;
-  }
-  bicycle_vjp<FAST>(xa, cst, p.inv_wheelbase, cx, gL, dv);  // k2 = f(xa), xa = x + dt/2 k1
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    mu0[i] += cx[i];
-    cst[i] = p.sixth_dt * mu[i] + p.half_dt * cx[i];
-    cx[i] = 0.0f;
-  }
-  bicycle_vjp<FAST>(xt, cst, p.inv_wheelbase, cx, gL, dv);  // k1 = f(x)
-#pragma unroll
-  for (int i = 0; i < N; ++i) mu0[i] += cx[i];
+}
+
+// The tracking cost's share of the costate of component i, whose distance to
+// the reference is d: weight w is Q_i (times the terminal scale at the end).
+__device__ __forceinline__ float track_grad(float a, float w, float d, float mu) {
+  return __builtin_fmaf(a * 2.0f * w, d, mu);
+}
+__device__ __forceinline__ float track_dq(float a, float d, float gq) {
+  return __builtin_fmaf(a * d, d, gq);
 }
 
 // d = (df/dx) xd: the bicycle derivative's tangent along xd at x (control
@@ -383,7 +396,7 @@ __device__ __forceinline__ int64_t tp_states_off(int tp_tiles, int nunit, int c,
          (static_cast<int64_t>(row) * kTileS + n) * tp_state_floats(c);
 }
 
-// Which units a workgroup of the sweep handles: in the segment-parallel mode
+// Which units row `row` of the sweep handles: in the segment-parallel mode
 // one (tile, unit) pair, units of `sub` per segment; otherwise one tile and
 // every segment (units = segments).
 struct SegSel {
@@ -391,17 +404,17 @@ struct SegSel {
   bool par;
 };
 
-__device__ __forceinline__ SegSel seg_select(int nseg, int c, int tp_tiles, int count) {
+__device__ __forceinline__ SegSel seg_select(int row, int nseg, int c, int tp_tiles, int count) {
   SegSel s;
   s.par = tp_tiles > 0 && count <= tp_tiles * kTileS;
   if (s.par) {
     s.sub = tp_sub(c);
     const int nunit = nseg * s.sub;
-    s.tile = blockIdx.x / nunit;
-    s.lo = s.hi = blockIdx.x % nunit;
+    s.tile = row / nunit;
+    s.lo = s.hi = row % nunit;
   } else {
     s.sub = 1;
-    s.tile = blockIdx.x;
+    s.tile = row;
     s.lo = 0;
     s.hi = nseg - 1;
   }
@@ -429,7 +442,7 @@ __device__ __forceinline__ void tp_chain(const DevParams& p, const float* __rest
   const float* last = tp + (static_cast<int64_t>(tile * nunit + nunit - 1) * kTileS + n) * kTpRec;
   const float* r = p.ref + static_cast<int64_t>(T) * N;
 #pragma unroll
-  for (int i = 0; i < N; ++i) mu[i] = a * 2.0f * p.w[16] * p.w[i] * (last[kTpXT + i] - r[i]);
+  for (int i = 0; i < N; ++i) mu[i] = track_grad(a, p.w[16] * p.w[i], last[kTpXT + i] - r[i], 0.0f);
   for (int s = nunit - 1; s > unit; --s) {
     const float* rec = tp + (static_cast<int64_t>(tile * nunit + s) * kTileS + n) * kTpRec;
     float m[N];
@@ -932,7 +945,7 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
   using f4 = mlp::f4;
   constexpr int N = 5, M = 2, H = 16 * MT;
   const int nseg = (T + c - 1) / c;
-  const SegSel sel = seg_select(nseg, c, tp_tiles, meta->count);
+  const SegSel sel = seg_select(blockIdx.x, nseg, c, tp_tiles, meta->count);
   const int nunit = nseg * sel.sub;
   const int base = sel.tile * kTileS;
   if (base >= meta->count) return;  // wave-uniform
@@ -1054,8 +1067,8 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const float d = xs[len * N + i] - r[i];
-        mu[i] = a * 2.0f * p.w[16] * p.w[i] * d;
-        gQ[i] += a * p.w[16] * d * d;
+        mu[i] = track_grad(a, p.w[16] * p.w[i], d, 0.0f);
+        gQ[i] = track_dq(a * p.w[16], d, gQ[i]);
       }
     }
     // the reference state after each step, requested one step ahead
@@ -1076,8 +1089,8 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const float d = xs[(j + 1) * N + i] - r[i];
-        mu[i] += a * 2.0f * p.w[i] * d;
-        gQ[i] += a * d * d;
+        mu[i] = track_grad(a, p.w[i], d, mu[i]);
+        gQ[i] = track_dq(a, d, gQ[i]);
       }
       float xt[N], v[M];
 #pragma unroll
@@ -1085,7 +1098,9 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
 #pragma unroll
       for (int q = 0; q < M; ++q) v[q] = vs[j * M + q];
       float mu0[N], dv[M] = {0.0f, 0.0f};
-      rk4_vjp<FAST>(p, xt, v, mu, mu0, gL, dv);
+      BicycleStages st;
+      bicycle_stages<FAST>(p, xt, v, st);
+      rk4_vjp(p, st, mu, mu0, gL, dv);
 
       if constexpr (MT > 0) {
         // residual dt g(z): c = dt mu_{t+1}
@@ -1197,27 +1212,45 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
   if (lane == 0) out[offQ + N] = sl;
 }
 
-// The sweep with the tile's MLP split over SW waves of one workgroup (SW = 2
-// or 4, H = 16 MT): wave w owns the TW = MT / SW hidden M-tiles q0 = w TW, ...
-// in every product, with its operand slices in registers (the weight packs
-// need no LDS):
-//   forward rebuild: h1 of the own tiles, then h2 of the own tiles over all of
-//     h1 (h1 tiles exchanged through LDS), output partials of the own K-tiles
-//     (exchanged);
-//   reverse: da2 of the own tiles = (W3^T c) d2; da1 of the own tiles =
-//     (W2^T da2) d1 over all da2 tiles (exchanged); dz partials of the own
-//     K-tiles (exchanged); dW2 / dW1 rows and dW3 columns of the own tiles as
-//     outer products over the tile's samples (the activations of all waves
-//     meet in the shared transposition buffer).
-// Every accumulation runs in the order of the one-wave sweep, so the
-// gradient is bitwise the same; the bicycle step and its transpose are
-// repeated by every wave.
-template <int MT, int SW>
+// The sweep with a tile's work divided over the waves of one workgroup (SW = 2
+// or 4, H = 16 MT).  MLP wave w (SW of them) owns the TW = MT / SW hidden M-tiles
+// q0 = w TW, ... in every product, with its operand slices in registers (the
+// weight packs need no LDS); the bicycle wave takes everything that is not a
+// product: the RK4 step and its transpose, the cost's gradient, dL/du and the
+// sums that belong to no weight.
+//   forward rebuild, per step (as the split rollout):
+//     h1 of the own tiles to LDS                                       barrier
+//     layer 2 over all of h1, output partials; the bicycle's increment barrier
+//     every wave: the new state
+//   reverse, per step:
+//     da2 of the own tiles = (W3^T c) d2 to LDS, the weight gradients of
+//     the step before                                                  barrier
+//     da1 of the own tiles = (W2^T da2) d1 over all of da2, W1^T partials,
+//     the activations to the transposition buffer; the bicycle's
+//     costate (dF/dx)^T mu, z and c                                    barrier
+//     every wave: the costate of the step before
+// The weight gradients (dW2 / dW1 rows and dW3 columns of the own tiles) are
+// outer products over the tile's samples through the transposition buffer.
+// Every accumulation runs in the order of the one-wave sweep, so the gradient
+// is bitwise the same.  Lane group g of an MLP wave carries component g of
+// the state (of the costate) and component 4, as in the split rollout.
+//
+// What bounds it is issue: binary32 MFMA and vector instructions of a SIMD do
+// not overlap, and with every wave repeating the bicycle's step and transpose
+// those took more of it than the products (46 MFMA a wave and reverse step).
+// T = 100, whole backward in us, every sample weighted, before and now: H = 64,
+// K = 4096 (one tile per CU) 378 -> 301, K = 8192 525 -> 467; H = 32 301 -> 232,
+// 415 -> 264; bfloat16 forward, H = 64, K = 8192 474 -> 417.
+constexpr int kSweepSlots = 2, kSweepCus = 256;
+constexpr int sweep_launch_waves(int SW) { return kSweepSlots * (SW + 1); }
+
+template <int MT, bool BF = false>
 struct SplitLds {
-  static constexpr int P = 64 * MT + 16;
-  static size_t bytes(int c) {
-    return sizeof(float) * (kTileS * P + kTileS * ((c + 1) * 5 + c * 2)) +
-           sizeof(mlp::f4) * 2 * 2 * MT * kWave;
+  static constexpr int P = 64 * MT + 16;  // transposition row stride (16 mod 32: no bank conflicts)
+  static constexpr int kOut = 12;         // floats per sample of an exchanged partial
+  __host__ __device__ static constexpr size_t bytes(int c) {
+    return sizeof(float) * (kTileS * P + kTileS * ((c + 1) * 5 + c * 2 + 8) + MT * kTileS * kOut) +
+           sizeof(mlp::f4) * (BF ? 2 : 1) * MT * kWave;
   }
 };
 
@@ -1225,7 +1258,8 @@ struct SplitLds {
 // kernel takes them (h2 tiles exchanged, the output over every K-block in
 // order), and the weight gradients over the rounded layer inputs.
 template <int MT, int SW, bool FAST, bool BF = false>
-__global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
+__global__ __launch_bounds__(kWave * sweep_launch_waves(SW), MT == 2 ? 4 : 2)
+    void adjoint_sweep_split_kernel(
     DevParams p, const float* __restrict__ u, const float* __restrict__ eps, int64_t ldk, int T,
     const float* __restrict__ ckpt, int c, const BwdItem* __restrict__ list,
     const BwdMeta* __restrict__ meta, float* __restrict__ partial, int64_t ngp, int du_off,
@@ -1234,83 +1268,211 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
   constexpr int TW = MT / SW;
   using f4 = mlp::f4;
   using PK = mlp::Pack<MT>;
-  constexpr int N = 5, M = 2, H = 16 * MT, PS = SplitLds<MT, SW>::P;
+  using L = SplitLds<MT, BF>;
+  constexpr int N = 5, M = 2, H = 16 * MT, PS = L::P;
   const int nseg = (T + c - 1) / c;
-  const SegSel sel = seg_select(nseg, c, tp_tiles, meta->count);
+  const int lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int n = lane % kTileS, g = lane / kTileS;
+  // the slot of the workgroup, the MLP wave's index in it (SW: the bicycle wave)
+  const int helper = SW;
+  const int slot = wave < kSweepSlots * SW ? wave / SW : wave - kSweepSlots * SW;
+  const int w = wave < kSweepSlots * SW ? wave % SW : helper;
+  const int b = static_cast<int>(blockIdx.x);
+  const int rowid = (b / kSweepCus * kSweepSlots + slot) * kSweepCus + b % kSweepCus;
+  const SegSel sel = seg_select(rowid, nseg, c, tp_tiles, meta->count);
   const int nunit = nseg * sel.sub;
   const int base = sel.tile * kTileS;
-  if (base >= meta->count) return;  // workgroup-uniform
+  if (base >= meta->count) return;  // the whole slot; the other one's barriers do not wait for it
   extern __shared__ float4 lds4[];
-  float* tb = reinterpret_cast<float*>(lds4);                             // [16][PS]
-  float* st_x = tb + kTileS * PS;                                         // states
-  f4* xa = reinterpret_cast<f4*>(st_x + kTileS * ((c + 1) * N + c * M));  // [2][MT][64]
-  f4* xb = xa + 2 * MT * kWave;                                           // [2][MT][64]
-  const int lane = threadIdx.x % kWave, w = threadIdx.x / kWave;
-  const int n = lane % kTileS, g = lane / kTileS;
-  const int q0 = w * TW;
+  // [MT][64]: h1 (or da2) tiles
+  f4* xh = reinterpret_cast<f4*>(reinterpret_cast<char*>(lds4) + slot * L::bytes(c));
+  f4* xg = xh + MT * kWave;                               // BF: [MT][64] h2 tiles
+  float* tb = reinterpret_cast<float*>(xg + (BF ? MT * kWave : 0));  // [16][PS]
+  float* xo = tb + kTileS * PS;                           // [MT][16][kOut]: partials
+  float* xq = xo + MT * kTileS * L::kOut;                 // [16][8]: the bicycle's share
+  float* st_x = xq + kTileS * 8;                          // states, then controls
   float* xs = st_x + n * ((c + 1) * N);
   float* vs = st_x + kTileS * (c + 1) * N + n * (c * M);
-  auto xch = [&](f4* buf, int par, int q) -> f4& { return buf[(par * MT + q) * kWave + lane]; };
+  auto part = [&](int tt, int i) -> float& { return xo[(tt * kTileS + n) * L::kOut + i]; };
 
-  // this wave's operand slices
-  const float* pf = p.mlp + lane;
-  const float* pb = p.mlp_bwd + lane;
-  constexpr int KB = mlp::PackBf<MT>::KB;
-  constexpr int TWF = BF ? 1 : TW, MTF = BF ? 1 : MT;
-  constexpr int TWB = BF ? TW : 1, KBB = BF ? KB : 1;
-  float fw1[TWF][2], fw2[TWF][MTF][4], fw3[TWF][4], bw3t[TW][2], bw2t[TW][MT][4], bw1t[TW][4];
-  mlp::bf8 v1[TWB], v2[TWB][KBB], v3[KBB];
-  f4 fb1[TW], fb2[TW], fb3[TW];
-#pragma unroll
-  for (int q = 0; q < TW; ++q) {
-    const int t = q0 + q;
-    if constexpr (BF) {
-      using PB = mlp::PackBf<MT>;
-      const uint4* bp = p.mlp_bf + lane;
-      v1[q] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW1 + t) * kWave]);
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-        v2[q][kb] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW2 + t * KB + kb) * kWave]);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if constexpr (!BF) fw1[q][j] = pf[(PK::kW1 + 2 * t + j) * kWave];
-      bw3t[q][j] = pb[(PK::kW3t + 2 * t + j) * kWave];
-    }
-#pragma unroll
-    for (int tt = 0; tt < MT; ++tt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (!BF) fw2[q][tt][i] = pf[(PK::kW2 + (t * MT + tt) * 4 + i) * kWave];
-        bw2t[q][tt][i] = pb[(PK::kW2t + (t * MT + tt) * 4 + i) * kWave];
-      }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if constexpr (!BF) fw3[q][i] = pf[(PK::kW3 + 4 * t + i) * kWave];
-      bw1t[q][i] = pb[(PK::kW1t + 4 * t + i) * kWave];
-      fb1[q][i] = pf[(PK::kB1 + 4 * t + i) * kWave];
-      fb2[q][i] = pf[(PK::kB2 + 4 * t + i) * kWave];
-      fb3[q][i] = (BF || t == 0) ? pf[(PK::kB3 + i) * kWave] : 0.0f;
-    }
-  }
-  if constexpr (BF) {
-    using PB = mlp::PackBf<MT>;
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-      v3[kb] = __builtin_bit_cast(mlp::bf8, p.mlp_bf[(PB::kW3 + kb) * kWave + lane]);
-  }
-
-  // this tile's pre-activation scratch: [c steps][2 layers][MT][64 lanes] f4
-  const int pre_steps = sel.par ? tp_unit_steps(c) : c;
-  f4* my_pre = pre + static_cast<int64_t>(blockIdx.x) * pre_steps * 2 * MT * kWave + lane;
   const int idx = base + n;
   const bool valid = idx < meta->count;
   const BwdItem item = list[valid ? idx : base];
   const int k = item.k;
-  const float a = valid ? item.a : 0.0f;
+  const float a = valid ? item.a : 0.0f;  // padding lanes rebuild a listed sample, weight 0
   const float* e = eps + k;
-
+  float* out = partial + static_cast<int64_t>(rowid) * ngp;
+  const int oB1 = 7 * H, oW2 = 8 * H, oB2 = 8 * H + H * H, oW3 = 9 * H + H * H,
+            oB3 = 14 * H + H * H, offQ = 14 * H + H * H + 5;
   const f4 zero4{0.0f, 0.0f, 0.0f, 0.0f};
+  float mu_in[N] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  if (sel.par && sel.hi < nunit - 1) tp_chain(p, tp, sel.tile, nunit, sel.hi, n, T, a, mu_in);
+
+  if (w == helper) {  // the bicycle wave
+    mlp::WeightsBf<MT> WB;  // BF: the output rows
+    if constexpr (BF) WB.load(p.mlp_bf, p.mlp, lane);
+    const float ic[2] = {p.is_coef[0], p.is_coef[1]};
+    float db3[N], gQ[N], gL = 0.0f, mu[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) { db3[i] = 0.0f; gQ[i] = 0.0f; mu[i] = mu_in[i]; }
+    if (sel.par && du_off >= 0) {
+      int sg, hp, ut0, ulen;
+      unit_steps(sel.hi, sel.sub, c, T, sg, hp, ut0, ulen);
+      tp_zero_du(out, du_off, T, ut0, ulen, lane, kWave);
+    }
+    for (int ui = sel.hi; ui >= sel.lo; --ui) {
+      int seg, hp, t0, len;
+      unit_steps(ui, sel.sub, c, T, seg, hp, t0, len);
+      if (sel.par) {
+        // the unit's states and controls as the map kernel kept them
+        if (g == 0)
+          copy_unit_forward(tp + tp_states_off(tp_tiles, nunit, c, sel.tile * nunit + ui, n), c,
+                            len, xs, vs);
+      } else {
+        float x[N], comp[N];
+        load_checkpoint(ckpt, ldk, k, seg, x, comp);
+        // u and the noise of a step are requested one step ahead
+        float un[M], en[M];
+        auto fetch_v = [&](int t) {
+#pragma unroll
+          for (int q = 0; q < M; ++q) {
+            un[q] = u[t * M + q];
+            en[q] = e[static_cast<int64_t>(t * M + q) * ldk];
+          }
+        };
+        if (len > 0) fetch_v(t0);
+        for (int j = 0; j < len; ++j) {
+          float v[M], q[N], res[N];
+#pragma unroll
+          for (int i = 0; i < M; ++i) v[i] = un[i] + en[i];
+          if (j + 1 < len) fetch_v(t0 + j + 1);
+          if (g == 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) xs[j * N + i] = x[i];
+#pragma unroll
+            for (int i = 0; i < M; ++i) vs[j * M + i] = v[i];
+          }
+          bicycle_increment_rows<FAST>(x, v, g, p, q, [] { __syncthreads(); });
+          if (g == 0) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) xq[n * 8 + i] = q[i];
+          }
+          __syncthreads();
+          if constexpr (BF) {
+            f4 h2[MT];
+#pragma unroll
+            for (int tt = 0; tt < MT; ++tt) h2[tt] = xg[tt * kWave + lane];
+            mlp::broadcast5(mlp::output_bf<MT>(WB, h2), n, res);
+          } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+              res[i] = part(0, i);
+#pragma unroll
+              for (int tt = 1; tt < MT; ++tt) res[i] += part(tt, i);
+            }
+          }
+          add_residual<kRK4>(x, comp, q, res, p);
+        }
+        if (g == 0) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) xs[len * N + i] = x[i];
+        }
+      }
+      __syncthreads();
+      if (ui == nunit - 1) {  // terminal cost w16 sum_i Q_i (x_T - r_T)^2
+        const float* r = p.ref + static_cast<int64_t>(T) * N;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const float d = xs[len * N + i] - r[i];
+          mu[i] = track_grad(a, p.w[16] * p.w[i], d, 0.0f);
+          gQ[i] = track_dq(a * p.w[16], d, gQ[i]);
+        }
+      }
+      float rn[N];  // the reference after a step, requested one step ahead
+      auto fetch_r = [&](int j) {
+        const float* r = p.ref + static_cast<int64_t>(t0 + j + 1) * N;
+#pragma unroll
+        for (int i = 0; i < N; ++i) rn[i] = r[i];
+      };
+      if (len > 0) fetch_r(len - 1);
+      for (int j = len - 1; j >= 0; --j) {
+        const int t = t0 + j;
+        float xt[N], v[M], cg[N], mu0[N], dv[M] = {0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+          const float d = xs[(j + 1) * N + i] - rn[i];
+          mu[i] = track_grad(a, p.w[i], d, mu[i]);
+          gQ[i] = track_dq(a, d, gQ[i]);
+          xt[i] = xs[j * N + i];
+          cg[i] = p.dt * mu[i];
+          db3[i] += cg[i];
+        }
+        if (j > 0) fetch_r(j - 1);
+#pragma unroll
+        for (int q = 0; q < M; ++q) v[q] = vs[j * M + q];
+        BicycleStages st;
+        bicycle_stages_rows<FAST>(p, xt, v, g, st);
+        __syncthreads();
+        rk4_vjp(p, st, mu, mu0, gL, dv);
+        if (g == 0) {
+#pragma unroll
+          for (int i = 0; i < N; ++i) xq[n * 8 + i] = mu0[i];
+        }
+        {  // z and c for the weight gradients
+          f4 zc = g == 0 ? f4{xt[0], xt[1], xt[2], xt[3]}
+                : g == 1 ? f4{xt[4], v[0], v[1], 0.0f}
+                : g == 2 ? f4{cg[0], cg[1], cg[2], cg[3]}
+                         : f4{cg[4], 0.0f, 0.0f, 0.0f};
+          if (BF && g < 2) zc = mlp::round_bf4(zc);
+          *reinterpret_cast<f4*>(tb + n * PS + 4 * H + 4 * g) = zc;
+        }
+        __syncthreads();
+        float dz[7];
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+          dz[i] = part(0, i);
+#pragma unroll
+          for (int tt = 1; tt < MT; ++tt) dz[i] += part(tt, i);
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) mu[i] = mu0[i] + dz[i];
+        dv[0] += dz[5];  // z rows 5, 6: the controls
+        dv[1] += dz[6];
+        if (du_off >= 0) du_step(p, ic, t, a, v, dv, lane, out + du_off + t * M);
+      }
+      __syncthreads();  // xs / vs are rewritten by the next segment
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const float s3 = group_sum(db3[i]);
+      if (lane == 0) out[oB3 + i] = s3;
+      const float sq = group_sum(gQ[i]);
+      if (lane == 0) out[offQ + i] = sq;
+    }
+    const float sl = group_sum(gL);
+    if (lane == 0) out[offQ + N] = sl;
+    return;
+  }
+
+  // an MLP wave
+  const int q0 = w * TW;
+  // output row m of an accumulator takes row m / 4 (m = 0 mod 4), row 4 (1 mod
+  // 4) and, of W1^T, rows 5 and 6 (2 and 3 mod 4) of the pack; padding is row 15
+  const int m3 = (n & 3) == 0 ? n / 4 : (n & 3) == 1 ? 4 : 15;
+  const int m1 = (n & 3) == 0 ? n / 4 : 3 + (n & 3);
+  // The operand slices of the rebuild and of the reverse pass are fetched anew
+  // for every unit (L1 / L2), so that the registers hold one set at a time: two
+  // workgroups of eight waves need at most 128 registers a lane.
+  auto fresh = [](const auto* ptr) {
+    asm volatile("" : "+s"(ptr));
+    return ptr;
+  };
+  constexpr int KB = mlp::PackBf<MT>::KB;
+
+  // this tile's pre-activation scratch: [c steps][2 layers][MT][64 lanes] f4
+  const int pre_steps = sel.par ? tp_unit_steps(c) : c;
+  f4* my_pre = pre + static_cast<int64_t>(rowid) * pre_steps * 2 * MT * kWave + lane;
   f4 dW1[TW], dW3[TW], db1[TW], db2[TW], dW2[TW][MT];
 #pragma unroll
   for (int q = 0; q < TW; ++q) {
@@ -1318,153 +1480,242 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
 #pragma unroll
     for (int nt = 0; nt < MT; ++nt) dW2[q][nt] = zero4;
   }
-  float db3[N], gQ[N], gL = 0.0f, mu[N];
+  // costate components g and 4 of the lane's sample, and their weights
+  float mua = g == 0 ? mu_in[0] : g == 1 ? mu_in[1] : g == 2 ? mu_in[2] : mu_in[3], mub = mu_in[4];
+  const float wa = g == 0 ? p.w[0] : g == 1 ? p.w[1] : g == 2 ? p.w[2] : p.w[3], wb = p.w[4];
+  // the weight gradients of a step: outer products over the tile's samples
+  auto outer = [&] {
 #pragma unroll
-  for (int i = 0; i < N; ++i) { db3[i] = 0.0f; gQ[i] = 0.0f; mu[i] = 0.0f; }
-  const float ic[2] = {p.is_coef[0], p.is_coef[1]};
-  int par = 0;
-
-  if (sel.par) {
-    if (sel.hi < nunit - 1) tp_chain(p, tp, sel.tile, nunit, sel.hi, n, T, a, mu);
-    if (du_off >= 0) {
-      int sg, hp, ut0, ulen;
-      unit_steps(sel.hi, sel.sub, c, T, sg, hp, ut0, ulen);
-      tp_zero_du(partial + static_cast<int64_t>(blockIdx.x) * ngp, du_off, T, ut0, ulen,
-                 threadIdx.x, blockDim.x);
+    for (int s4 = 0; s4 < 4; ++s4) {
+      const float* tq = tb + (4 * s4 + g) * PS;
+      const float bz = tq[4 * H + n];
+      const float ac = n < 8 ? tq[4 * H + 8 + n] : 0.0f;
+      float bh1[MT];
+#pragma unroll
+      for (int nt = 0; nt < MT; ++nt) bh1[nt] = tq[16 * nt + n];
+#pragma unroll
+      for (int q = 0; q < TW; ++q) {
+        const int qt = q0 + q;
+        const float ad2 = tq[3 * H + 16 * qt + n];
+        const float ad1 = tq[2 * H + 16 * qt + n];
+        const float bh2 = tq[H + 16 * qt + n];
+#pragma unroll
+        for (int nt = 0; nt < MT; ++nt) dW2[q][nt] = mlp::mfma(ad2, bh1[nt], dW2[q][nt]);
+        dW1[q] = mlp::mfma(ad1, bz, dW1[q]);
+        dW3[q] = mlp::mfma(ac, bh2, dW3[q]);
+      }
     }
-  }
+  };
+
   for (int ui = sel.hi; ui >= sel.lo; --ui) {
     int seg, hp, t0, len;
     unit_steps(ui, sel.sub, c, T, seg, hp, t0, len);
-    if (sel.par) {
-      // the unit's states, controls and pre-activations as the map kernel kept them
-      if (w == 0 && g == 0)
-        copy_unit_forward(tp + tp_states_off(tp_tiles, nunit, c, sel.tile * nunit + ui, n), c,
-                          len, xs, vs);
-    } else {
-      float x[N], comp[N];
-      load_checkpoint(ckpt, ldk, k, seg, x, comp);
-      // u and the noise of a step are requested one step ahead, so their
-      // latency hides behind the previous step's work (barriers wait for LDS
-      // only, not for these loads)
-      float un[M], en[M];
-      auto fetch_v = [&](int t) {
-  #pragma unroll
-        for (int q = 0; q < M; ++q) {
-          un[q] = u[t * M + q];
-          en[q] = e[static_cast<int64_t>(t * M + q) * ldk];
+    if (!sel.par) {
+      const float* ck = ckpt + static_cast<int64_t>(seg) * 7 * ldk + k;
+      const float* pw = fresh(p.mlp);
+      const float* pf = pw + lane;
+      f4 fb1[TW], fb2[TW];
+#pragma unroll
+      for (int q = 0; q < TW; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          fb1[q][i] = pf[(PK::kB1 + 4 * (q0 + q) + i) * kWave];
+          fb2[q][i] = pf[(PK::kB2 + 4 * (q0 + q) + i) * kWave];
         }
-      };
-      if (len > 0) fetch_v(t0);
-      for (int j = 0; j < len; ++j) {
-        const int t = t0 + j;
-        float v[M];
-  #pragma unroll
-        for (int q = 0; q < M; ++q) v[q] = un[q] + en[q];
-        if (j + 1 < len) fetch_v(t + 1);
-        if (w == 0 && g == 0) {
-  #pragma unroll
-          for (int i = 0; i < N; ++i) xs[j * N + i] = x[i];
-  #pragma unroll
-          for (int q = 0; q < M; ++q) vs[j * M + q] = v[q];
+      if constexpr (BF) {
+        using PB = mlp::PackBf<MT>;
+        const uint4* bp = fresh(p.mlp_bf) + lane;
+        mlp::bf8 v1[TW], v2[TW][KB], v3[KB];
+#pragma unroll
+        for (int q = 0; q < TW; ++q) {
+          v1[q] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW1 + q0 + q) * kWave]);
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+            v2[q][kb] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW2 + (q0 + q) * KB + kb) * kWave]);
         }
-        // MLP forward, split (as the split forward kernel)
-        f4* ps = my_pre + static_cast<int64_t>(j) * 2 * MT * kWave;
-        if constexpr (BF) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+          v3[kb] = __builtin_bit_cast(mlp::bf8, bp[(PB::kW3 + kb) * kWave]);
+        f4 fb3;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) fb3[i] = pf[(PK::kB3 + i) * kWave];
+        // lane group 0 carries the state (the others' copies are never used)
+        float x[N], comp[N];
+        load_checkpoint(ckpt, ldk, k, seg, x, comp);
+        float un[M], en[M];
+        auto fetch_v = [&](int t) {
+#pragma unroll
+          for (int q = 0; q < M; ++q) {
+            un[q] = u[t * M + q];
+            en[q] = e[static_cast<int64_t>(t * M + q) * ldk];
+          }
+        };
+        if (len > 0) fetch_v(t0);
+        for (int j = 0; j < len; ++j) {
+          float v[M];
+#pragma unroll
+          for (int q = 0; q < M; ++q) v[q] = un[q] + en[q];
+          if (j + 1 < len) fetch_v(t0 + j + 1);
+          f4* ps = my_pre + static_cast<int64_t>(j) * 2 * MT * kWave;
           const mlp::bf8 zb = mlp::input_operand_bf(x, v, g);
-  #pragma unroll
+#pragma unroll
           for (int q = 0; q < TW; ++q) {
             const f4 a1 = mlp::mfma_bf(v1[q], zb, fb1[q]);
             ps[(q0 + q) * kWave] = a1;
-            xch(xa, par, q0 + q) = mlp::tanh4(a1);
-          }
-        } else {
-          const float z0 = mlp::input_operand(x, v, g, 0), z1 = mlp::input_operand(x, v, g, 1);
-  #pragma unroll
-          for (int q = 0; q < TW; ++q) {
-            const f4 a1 = mlp::mfma(fw1[q][1], z1, mlp::mfma(fw1[q][0], z0, fb1[q]));
-            ps[(q0 + q) * kWave] = a1;
-            xch(xa, par, q0 + q) = mlp::tanh4(a1);
-          }
-        }
-        __syncthreads();
-        f4 acc[TW];
-  #pragma unroll
-        for (int q = 0; q < TW; ++q) acc[q] = fb2[q];
-        f4 out;
-        if constexpr (BF) {
-          f4 h1a[MT];
-  #pragma unroll
-          for (int tt = 0; tt < MT; ++tt) h1a[tt] = xch(xa, par, tt);
-  #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) {
-            const mlp::bf8 hb = mlp::kblock_operand<MT>(h1a, kb);
-  #pragma unroll
-            for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma_bf(v2[q][kb], hb, acc[q]);
-          }
-  #pragma unroll
-          for (int q = 0; q < TW; ++q) {
-            ps[(MT + q0 + q) * kWave] = acc[q];
-            xch(xb, par, q0 + q) = mlp::tanh4(acc[q]);
+            xh[(q0 + q) * kWave + lane] = mlp::tanh4(a1);
           }
           __syncthreads();
-          f4 h2a[MT];
-  #pragma unroll
-          for (int tt = 0; tt < MT; ++tt) h2a[tt] = xch(xb, par, tt);
-          out = fb3[0];
-  #pragma unroll
-          for (int kb = 0; kb < KB; ++kb) out = mlp::mfma_bf(v3[kb], mlp::kblock_operand<MT>(h2a, kb), out);
-        } else {
-  #pragma unroll
-          for (int tt = 0; tt < MT; ++tt) {
-            const f4 h = xch(xa, par, tt);
-  #pragma unroll
-            for (int i = 0; i < 4; ++i)
-  #pragma unroll
-              for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma(fw2[q][tt][i], h[i], acc[q]);
+          f4 hh[MT];
+#pragma unroll
+          for (int tt = 0; tt < MT; ++tt) hh[tt] = xh[tt * kWave + lane];
+          f4 acc[TW];
+#pragma unroll
+          for (int q = 0; q < TW; ++q) acc[q] = fb2[q];
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb) {
+            const mlp::bf8 hb = mlp::kblock_operand<MT>(hh, kb);
+#pragma unroll
+            for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma_bf(v2[q][kb], hb, acc[q]);
           }
-  #pragma unroll
+#pragma unroll
+          for (int q = 0; q < TW; ++q) {
+            ps[(MT + q0 + q) * kWave] = acc[q];
+            xg[(q0 + q) * kWave + lane] = mlp::tanh4(acc[q]);
+          }
+          __syncthreads();
+          float qi[N], res[N];
+#pragma unroll
+          for (int i = 0; i < N; ++i) qi[i] = xq[n * 8 + i];
+#pragma unroll
+          for (int tt = 0; tt < MT; ++tt) hh[tt] = xg[tt * kWave + lane];
+          f4 o = fb3;
+#pragma unroll
+          for (int kb = 0; kb < KB; ++kb)
+            o = mlp::mfma_bf(v3[kb], mlp::kblock_operand<MT>(hh, kb), o);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) res[i] = o[i];
+          const uint32_t o0 = __float_as_uint(o[0]);
+          res[4] = __uint_as_float(__builtin_amdgcn_permlane16_swap(o0, o0, false, false)[1]);
+          add_residual<kRK4>(x, comp, qi, res, p);
+        }
+      } else {
+        const float* pf3 = pw + kTileS * g + m3;
+        float fw1[TW][2], fw2[TW][MT][4], fw3[TW][4];
+        f4 fb3[TW];
+#pragma unroll
+        for (int q = 0; q < TW; ++q) {
+          const int t = q0 + q;
+          fw1[q][0] = pf[(PK::kW1 + 2 * t) * kWave];
+          fw1[q][1] = pf[(PK::kW1 + 2 * t + 1) * kWave];
+#pragma unroll
+          for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) fw2[q][tt][i] = pf[(PK::kW2 + (t * MT + tt) * 4 + i) * kWave];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) fw3[q][i] = pf3[(PK::kW3 + 4 * t + i) * kWave];
+          fb3[q] = zero4;
+          if (t == 0) {
+            fb3[q][0] = pw[(PK::kB3 + g) * kWave];
+            fb3[q][1] = pw[PK::kB3 * kWave + kTileS];
+          }
+        }
+        float xa = ck[g * ldk], xb = ck[4 * ldk], ca = g < 2 ? ck[(5 + g) * ldk] : 0.0f;
+        const int jc = g == 2 ? 1 : 0;  // the control the lane group's input slot takes
+        float un = 0.0f, en = 0.0f;
+        auto fetch_v = [&](int t) {
+          un = u[t * M + jc];
+          en = e[static_cast<int64_t>(t * M + jc) * ldk];
+        };
+        if (len > 0) fetch_v(t0);
+        for (int j = 0; j < len; ++j) {
+          const float v = un + en;
+          if (j + 1 < len) fetch_v(t0 + j + 1);
+          f4* ps = my_pre + static_cast<int64_t>(j) * 2 * MT * kWave;
+          const float z1 = g == 0 ? xb : g == 3 ? 0.0f : v;
+#pragma unroll
+          for (int q = 0; q < TW; ++q) {
+            const f4 a1 = mlp::mfma(fw1[q][1], z1, mlp::mfma(fw1[q][0], xa, fb1[q]));
+            ps[(q0 + q) * kWave] = a1;
+            xh[(q0 + q) * kWave + lane] = mlp::tanh4(a1);
+          }
+          __syncthreads();
+          f4 h1[MT], acc[TW];
+#pragma unroll
+          for (int tt = 0; tt < MT; ++tt) h1[tt] = xh[tt * kWave + lane];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int q = 0; q < TW; ++q) acc[q] = fb2[q];
+#pragma unroll
+          for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+              for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma(fw2[q][tt][i], h1[tt][i], acc[q]);
+#pragma unroll
           for (int q = 0; q < TW; ++q) {
             ps[(MT + q0 + q) * kWave] = acc[q];
             const f4 h2 = mlp::tanh4(acc[q]);
-            f4 part = fb3[q];
-  #pragma unroll
-            for (int i = 0; i < 4; ++i) part = mlp::mfma(fw3[q][i], h2[i], part);
-            xch(xb, par, q0 + q) = part;
+            __builtin_amdgcn_sched_barrier(0);
+            f4 o = fb3[q];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o = mlp::mfma(fw3[q][i], h2[i], o);
+            part(q0 + q, g) = o[0];
+            if (g == 0) part(q0 + q, 4) = o[1];
           }
           __syncthreads();
-          out = xch(xb, par, 0);
-  #pragma unroll
-          for (int tt = 1; tt < MT; ++tt) out += xch(xb, par, tt);
+          float ra = part(0, g), rb = part(0, 4);
+#pragma unroll
+          for (int tt = 1; tt < MT; ++tt) {
+            ra += part(tt, g);
+            rb += part(tt, 4);
+          }
+          const float qa = xq[n * 8 + g], qb = xq[n * 8 + 4];
+          {
+#pragma clang fp contract(off)
+            // add_residual for components g and 4
+            const float h = inc_scale<kRK4>(p);
+            const float ia =
+                g < 3 ? __builtin_fmaf(p.dt, ra, qa) : __builtin_fmaf(h, qa, p.dt * ra);
+            const float y = ia - ca;
+            const float s = xa + y;
+            ca = g < 2 ? (s - xa) - y : 0.0f;
+            xa = s;
+            xb = xb + __builtin_fmaf(h, qb, p.dt * rb);
+          }
         }
-        par ^= 1;
-        float res[N];
-        mlp::broadcast5(out, n, res);
-        residual_step<FAST, kRK4>(x, v, comp, p, res);
-      }
-      if (w == 0 && g == 0) {
-  #pragma unroll
-        for (int i = 0; i < N; ++i) xs[len * N + i] = x[i];
       }
     }
-    __syncthreads();
+    __syncthreads();  // the unit's states and controls are in LDS
+    float bw3t[TW][2], bw2t[TW][MT][4], bw1t[TW][4];
+    {
+      const float* pb = fresh(p.mlp_bwd) + lane;
+      const float* pb1 = pb - lane + kTileS * g + m1;
+#pragma unroll
+      for (int q = 0; q < TW; ++q) {
+        const int t = q0 + q;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) bw3t[q][j] = pb[(PK::kW3t + 2 * t + j) * kWave];
+#pragma unroll
+        for (int tt = 0; tt < MT; ++tt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) bw2t[q][tt][i] = pb[(PK::kW2t + (t * MT + tt) * 4 + i) * kWave];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bw1t[q][i] = pb1[(PK::kW1t + 4 * t + i) * kWave];
+      }
+    }
     if (ui == nunit - 1) {
       const float* r = p.ref + static_cast<int64_t>(T) * N;
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const float d = xs[len * N + i] - r[i];
-        mu[i] = a * 2.0f * p.w[16] * p.w[i] * d;
-        gQ[i] += a * p.w[16] * d * d;
-      }
+      mua = track_grad(a, p.w[16] * wa, xs[len * N + g] - r[g], 0.0f);
+      mub = track_grad(a, p.w[16] * wb, xs[len * N + 4] - r[4], 0.0f);
     }
     // the reference state after the step and the step's MLP pre-activations,
-    // requested one step ahead like the forward's noise
-    float rn[N];
+    // requested one step ahead
+    float rna = 0.0f, rnb = 0.0f;
     f4 pn1[TW], pn2[TW];
     auto fetch_r = [&](int j) {
       const float* r = p.ref + static_cast<int64_t>(t0 + j + 1) * N;
-#pragma unroll
-      for (int i = 0; i < N; ++i) rn[i] = r[i];
+      rna = r[g];
+      rnb = r[4];
       const f4* ps = my_pre + static_cast<int64_t>(j) * 2 * MT * kWave;
 #pragma unroll
       for (int q = 0; q < TW; ++q) {
@@ -1474,137 +1725,74 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
     };
     if (len > 0) fetch_r(len - 1);
     for (int j = len - 1; j >= 0; --j) {
-      const int t = t0 + j;
-      float r[N];
-      f4 pa1[TW], pa2[TW];
-#pragma unroll
-      for (int i = 0; i < N; ++i) r[i] = rn[i];
+      mua = track_grad(a, wa, xs[(j + 1) * N + g] - rna, mua);
+      mub = track_grad(a, wb, xs[(j + 1) * N + 4] - rnb, mub);
+      // the MLP residual dt g(z): c = dt mu_{t+1}
+      f4 h1[TW], d1[TW], h2[TW], d2[TW], da2[TW];
 #pragma unroll
       for (int q = 0; q < TW; ++q) {
-        pa1[q] = pn1[q];
-        pa2[q] = pn2[q];
+        mlp::tanh4_d(pn1[q], h1[q], d1[q]);
+        mlp::tanh4_d(pn2[q], h2[q], d2[q]);
       }
       if (j > 0) fetch_r(j - 1);
-#pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const float d = xs[(j + 1) * N + i] - r[i];
-        mu[i] += a * 2.0f * p.w[i] * d;
-        gQ[i] += a * d * d;
-      }
-      float xt[N], v[M];
-#pragma unroll
-      for (int i = 0; i < N; ++i) xt[i] = xs[j * N + i];
-#pragma unroll
-      for (int q = 0; q < M; ++q) v[q] = vs[j * M + q];
-      float mu0[N], dv[M] = {0.0f, 0.0f};
-      rk4_vjp<FAST>(p, xt, v, mu, mu0, gL, dv);
-      // the MLP residual dt g(z): c = dt mu_{t+1}
-      f4 h1[TW], d1[TW], h2[TW], d2[TW];
-#pragma unroll
-      for (int q = 0; q < TW; ++q) {
-        mlp::tanh4_d(pa1[q], h1[q], d1[q]);
-        mlp::tanh4_d(pa2[q], h2[q], d2[q]);
-      }
-      float cg[N];
-#pragma unroll
-      for (int i = 0; i < N; ++i) cg[i] = p.dt * mu[i];
-      const float c0 = g == 0 ? cg[0] : g == 1 ? cg[1] : g == 2 ? cg[2] : cg[3];
-      const float c1 = g == 0 ? cg[4] : 0.0f;
-      f4 da2[TW];
+      const float c0 = p.dt * mua, c1 = g == 0 ? p.dt * mub : 0.0f;
 #pragma unroll
       for (int q = 0; q < TW; ++q) {
         da2[q] = mlp::mfma(bw3t[q][1], c1, mlp::mfma(bw3t[q][0], c0, zero4)) * d2[q];
-        xch(xa, par, q0 + q) = da2[q];
+        xh[(q0 + q) * kWave + lane] = da2[q];
       }
+      // the weight gradients of the step before run while da2 travels
+      if (j + 1 < len) outer();
       __syncthreads();
-      f4 acc[TW];
+      f4 dd[MT], acc[TW];
+#pragma unroll
+      for (int tt = 0; tt < MT; ++tt) dd[tt] = xh[tt * kWave + lane];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < TW; ++q) acc[q] = zero4;
 #pragma unroll
-      for (int tt = 0; tt < MT; ++tt) {
-        const f4 d = xch(xa, par, tt);
+      for (int tt = 0; tt < MT; ++tt)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma(bw2t[q][tt][i], d[i], acc[q]);
-      }
+          for (int q = 0; q < TW; ++q) acc[q] = mlp::mfma(bw2t[q][tt][i], dd[tt][i], acc[q]);
       float* row = tb + n * PS;
-      f4 da1[TW];
 #pragma unroll
       for (int q = 0; q < TW; ++q) {
-        da1[q] = acc[q] * d1[q];
+        const f4 da1 = acc[q] * d1[q];
         f4 zp = zero4;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) zp = mlp::mfma(bw1t[q][i], da1[q][i], zp);
-        xch(xb, par, q0 + q) = zp;
+        for (int i = 0; i < 4; ++i) zp = mlp::mfma(bw1t[q][i], da1[i], zp);
         // the transposition buffer: the own rows
         const int qt = q0 + q;
         *reinterpret_cast<f4*>(row + 16 * qt + 4 * g) = BF ? mlp::round_bf4(h1[q]) : h1[q];
         *reinterpret_cast<f4*>(row + H + 16 * qt + 4 * g) = BF ? mlp::round_bf4(h2[q]) : h2[q];
-        *reinterpret_cast<f4*>(row + 2 * H + 16 * qt + 4 * g) = da1[q];
+        *reinterpret_cast<f4*>(row + 2 * H + 16 * qt + 4 * g) = da1;
         *reinterpret_cast<f4*>(row + 3 * H + 16 * qt + 4 * g) = da2[q];
-      }
-      if (w == 0) {  // z and c
-        f4 zc = g == 0 ? f4{xt[0], xt[1], xt[2], xt[3]}
-              : g == 1 ? f4{xt[4], v[0], v[1], 0.0f}
-              : g == 2 ? f4{cg[0], cg[1], cg[2], cg[3]}
-                       : f4{cg[4], 0.0f, 0.0f, 0.0f};
-        if (BF && g < 2) zc = mlp::round_bf4(zc);
-        *reinterpret_cast<f4*>(row + 4 * H + 4 * g) = zc;
-      }
-      __syncthreads();
-      f4 dz = xch(xb, par, 0);
-#pragma unroll
-      for (int tt = 1; tt < MT; ++tt) dz += xch(xb, par, tt);
-      par ^= 1;
-      float dzs[N];
-      mlp::broadcast5(dz, n, dzs);
-#pragma unroll
-      for (int i = 0; i < N; ++i) mu0[i] += dzs[i];
-      dv[0] += __shfl(dz[1], 16 + n, kWave);  // z rows 5, 6: the controls
-      dv[1] += __shfl(dz[2], 16 + n, kWave);
-#pragma unroll
-      for (int q = 0; q < TW; ++q) {
-        db1[q] += da1[q];
+        db1[q] += da1;
         db2[q] += da2[q];
-      }
-      if (w == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) db3[i] += cg[i];
-      }
-#pragma unroll
-      for (int s4 = 0; s4 < 4; ++s4) {
-        const float* tq = tb + (4 * s4 + g) * PS;
-        const float bz = tq[4 * H + n];
-        const float ac = n < 8 ? tq[4 * H + 8 + n] : 0.0f;
-        float bh1[MT];
-#pragma unroll
-        for (int nt = 0; nt < MT; ++nt) bh1[nt] = tq[16 * nt + n];
-#pragma unroll
-        for (int q = 0; q < TW; ++q) {
-          const int qt = q0 + q;
-          const float ad2 = tq[3 * H + 16 * qt + n];
-          const float ad1 = tq[2 * H + 16 * qt + n];
-          const float bh2 = tq[H + 16 * qt + n];
-#pragma unroll
-          for (int nt = 0; nt < MT; ++nt) dW2[q][nt] = mlp::mfma(ad2, bh1[nt], dW2[q][nt]);
-          dW1[q] = mlp::mfma(ad1, bz, dW1[q]);
-          dW3[q] = mlp::mfma(ac, bh2, dW3[q]);
+        part(qt, g) = zp[0];
+        if (g == 0) {
+          part(qt, 4) = zp[1];
+          part(qt, 5) = zp[2];
+          part(qt, 6) = zp[3];
         }
       }
-      __syncthreads();  // the transposition buffer is rewritten by the next step
-      if (du_off >= 0 && w == 0)
-        du_step(p, ic, t, a, v, dv, lane, partial + blockIdx.x * ngp + du_off + t * M);
+      __syncthreads();
+      float dza = part(0, g), dzb = part(0, 4);
 #pragma unroll
-      for (int i = 0; i < N; ++i) mu[i] = mu0[i];
+      for (int tt = 1; tt < MT; ++tt) {
+        dza += part(tt, g);
+        dzb += part(tt, 4);
+      }
+      mua = xq[n * 8 + g] + dza;
+      mub = xq[n * 8 + 4] + dzb;
     }
+    if (len > 0) outer();
     __syncthreads();  // xs / vs are rewritten by the next segment
   }
 
   // this tile's partial gradient: [W1 | b1 | W2 | b2 | W3 | b3 | Q | wheelbase]
-  float* out = partial + static_cast<int64_t>(blockIdx.x) * ngp;
-  const int oB1 = 7 * H, oW2 = 8 * H, oB2 = 8 * H + H * H, oW3 = 9 * H + H * H,
-            oB3 = 14 * H + H * H, offQ = 14 * H + H * H + 5;
 #pragma unroll
   for (int q = 0; q < TW; ++q) {
     const int qt = q0 + q;
@@ -1620,17 +1808,6 @@ __global__ __launch_bounds__(kWave * SW) void adjoint_sweep_split_kernel(
       const float s2 = group_sum(db2[q][i]);
       if (n == 0) { out[oB1 + r] = s1; out[oB2 + r] = s2; }
     }
-  }
-  if (w == 0) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const float s3 = group_sum(db3[i]);
-      if (lane == 0) out[oB3 + i] = s3;
-      const float sq = group_sum(gQ[i]);
-      if (lane == 0) out[offQ + i] = sq;
-    }
-    const float sl = group_sum(gL);
-    if (lane == 0) out[offQ + N] = sl;
   }
 }
 
@@ -1797,16 +1974,17 @@ hipError_t launch_adjoint(const DevParams& p, bool accurate_trig, int hidden, co
   if (waves > 1) {
     if (hidden == 64 && waves == 4) {
       fn = pick_split_sweep<4, 4>(accurate_trig, bf);
-      lds = SplitLds<4, 4>::bytes(ckpt_every);
+      lds = bf ? SplitLds<4, true>::bytes(ckpt_every) : SplitLds<4>::bytes(ckpt_every);
     } else if (hidden == 64 && waves == 2) {
       fn = pick_split_sweep<4, 2>(accurate_trig, bf);
-      lds = SplitLds<4, 2>::bytes(ckpt_every);
+      lds = bf ? SplitLds<4, true>::bytes(ckpt_every) : SplitLds<4>::bytes(ckpt_every);
     } else if (hidden == 32 && waves == 2) {
       fn = pick_split_sweep<2, 2>(accurate_trig, bf);
-      lds = SplitLds<2, 2>::bytes(ckpt_every);
+      lds = bf ? SplitLds<2, true>::bytes(ckpt_every) : SplitLds<2>::bytes(ckpt_every);
     } else {
       return hipErrorInvalidValue;
     }
+    lds *= kSweepSlots;
   } else {
     switch (hidden) {
       case 0: fn = pick_sweep<0>(accurate_trig); break;
@@ -1849,7 +2027,11 @@ hipError_t launch_adjoint(const DevParams& p, bool accurate_trig, int hidden, co
                        d_eps, ldk, T, d_ckpt, ckpt_every, list, meta, tp, tpbuf, pre);
   }
   const int rows = std::max(tiles, tp * nunit);
-  hipLaunchKernelGGL(fn, dim3(rows), dim3(kWave * waves), lds, stream, p, d_u, d_eps, ldk, T,
+  // the split sweep's workgroup b takes rows 512 (b / 256) + b mod 256 and that + 256
+  constexpr int kGroup = kSweepSlots * kSweepCus;
+  const int grid = waves == 1 || rows <= kSweepCus ? rows : (rows + kGroup - 1) / kGroup * kSweepCus;
+  hipLaunchKernelGGL(fn, dim3(grid),
+                     dim3(kWave * (waves > 1 ? sweep_launch_waves(waves) : 1)), lds, stream, p, d_u, d_eps, ldk, T,
                      d_ckpt, ckpt_every, list, meta, partial, s.ngp, du_off, pre, tpbuf, tp);
   hipLaunchKernelGGL(adjoint_reduce_kernel, dim3((ncols + kReduceCols - 1) / kReduceCols),
                      dim3(kReduceCols * kReduceParts), 0, stream, partial, s.ngp, ngrad, ncols,

@@ -152,7 +152,9 @@ __global__ __launch_bounds__(kWave * split_launch_waves(SW)) void rollout_tile_s
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * M, lds);
   const int lane = threadIdx.x % kWave;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  constexpr int kCus = 256;
+  const int turn = static_cast<int>(blockIdx.x / kCus) & 1;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) ^ (SW == 2 ? 2 * turn : 0);
   const int n = lane % kTile, g = lane / kTile;
   const int k = blockIdx.x * kTile + n;
   const bool live = k < K;
@@ -163,9 +165,7 @@ __global__ __launch_bounds__(kWave * split_launch_waves(SW)) void rollout_tile_s
   const float* e = eps + (live ? k : K - 1);
 
   if (w >= SW) {  // a helper wave
-    constexpr int kCus = 256;
-    const int turn = SW == 4 ? (blockIdx.x / kCus) & 1 : 0;
-    const int bicycle = SW + turn, cost = SW + turn + (SW == 4 ? 2 : 1);
+    const int bicycle = SW == 4 ? SW + turn : SW, cost = SW == 4 ? SW + turn + 2 : SW + 1;
     if (w != bicycle && w != cost) return;
     float x[N], comp[N];
 #pragma unroll
