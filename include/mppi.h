@@ -450,6 +450,18 @@ mppi_status mppi_iterate(mppi_ctx* ctx, int32_t num_iters);
  * EINVAL (NULL). */
 mppi_status mppi_get_controls(mppi_ctx* ctx, float* d_U);
 
+/* ---- ordering with the caller's streams -----------------------------------
+ * For callers whose tensors live on other streams than the context's (one event
+ * each way, kept by the context; nothing waits on the host; a stream of the
+ * context's device):
+ *   mppi_wait_stream    what the context is given from now on starts after
+ *                       everything hip_stream holds now;
+ *   mppi_release_stream what hip_stream is given from now on starts after
+ *                       everything the context has been given.
+ * Errors: EINVAL (NULL ctx), EDEVICE. */
+mppi_status mppi_wait_stream(mppi_ctx* ctx, void* hip_stream);
+mppi_status mppi_release_stream(mppi_ctx* ctx, void* hip_stream);
+
 enum {
   MPPI_DEBUG_NOISE = 0,   /* float eps[T][m][K] of the last sampling */
   MPPI_DEBUG_COSTS = 1,   /* float J[K] of the last rollout (or set_costs) */

@@ -3,9 +3,20 @@
 PyTorch supplies the device memory (the workspace and the x0 / u / U buffers)
 and a HIP stream; the arithmetic of every step of the iteration runs in
 libmppi.so's kernels.  The controller works on a stream of its own (default
-priority) so that `iterate` can replay a captured hipGraph; every call first
-orders that stream after torch's current stream, and every tensor it returns
-is ordered back onto torch's current stream, so callers can ignore streams.
+priority) so that `iterate` can replay a captured hipGraph.  A call that reads a
+caller's tensor first orders that stream after torch's current stream, and
+every tensor a call returns is ordered back onto torch's current stream, so
+callers can ignore streams; the other calls (shift, sample, rollout, update,
+iterate, set_iteration) touch only the context's own memory and follow each other
+on its stream (while torch's current stream is under capture they are ordered
+after it too, which makes them part of the capture).
+
+The ordering uses the library's two events (mppi_wait_stream,
+mppi_release_stream): a torch Stream.wait_stream makes a new event and costs 19 us
+of host time, and a control call made four of them.  Returned tensors belong to
+torch's current stream: they are allocated there before the library's stream is
+ordered after it, and that stream is ordered after the library's work on them, so
+their memory is never reused early.
 
 A list of problems makes a batch context: all instances advance together,
 one launch per phase.  Per-instance arrays are then packed in instance order
@@ -21,6 +32,10 @@ import torch
 
 from . import _abi
 from ._abi import check, lib
+
+
+# handle of torch's current stream on a device, without making a Stream object
+_raw_stream = torch._C._cuda_getCurrentRawStream
 
 
 def _fptr(a: np.ndarray):
@@ -145,7 +160,7 @@ class Controller:
         if nbytes == 0:
             raise _abi.MPPIError(_abi.MPPI_EINVAL, L.mppi_last_error().decode())
         self.stream = stream if stream is not None else torch.cuda.Stream(self.device)
-        self._enter()
+        self.stream.wait_stream(torch.cuda.current_stream(self.device))
         ctx = C.c_void_p()
         if static_workspace:
             if self.batch:
@@ -165,29 +180,53 @@ class Controller:
                                     self.workspace.data_ptr(), nbytes, self.stream.cuda_stream,
                                     C.byref(ctx)))
         self.ctx = ctx
+        self._lib = L
+        # where a tensor has to live to be handed to the library as it is
+        self._dev_exact = torch.empty(0, device=self.device).device
         self._off = {k: self._offsets(k) for k in (_abi.PACKED_STATE, _abi.PACKED_CONTROLS,
                                                    _abi.PACKED_SAMPLES, _abi.PACKED_NOISE)}
         self.set_state(np.concatenate([np.asarray(q.x0, np.float32).ravel() for q in probs]))
         self.set_controls(np.concatenate([np.asarray(q.u0, np.float32).ravel() for q in probs]))
 
     # -- streams ------------------------------------------------------------
-    def _enter(self):
+    def _current(self) -> int:
+        """Handle of torch's current stream on the controller's device."""
+        i = self.device.index
+        return _raw_stream(torch.cuda.current_device() if i is None else i)
+
+    def _capturing(self) -> bool:
+        return torch.cuda.is_current_stream_capturing()
+
+    def _enter(self) -> None:
         """Order the library's stream after torch's current stream."""
-        self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        if self._capturing():
+            self.stream.wait_stream(torch.cuda.current_stream(self.device))
+        else:
+            check(self._lib.mppi_wait_stream(self.ctx, self._current()))
+
+    def _own(self) -> None:
+        """Before a call that reads none of the caller's tensors: only a capture
+        of torch's current stream has to be joined."""
+        if self._capturing():
+            self._enter()
 
     def _leave(self, t: torch.Tensor) -> torch.Tensor:
-        """Order torch's current stream after the library's work on t."""
-        cur = torch.cuda.current_stream(self.device)
-        cur.wait_stream(self.stream)
-        t.record_stream(cur)
+        """Order torch's current stream after the library's work on t, which was
+        allocated on that stream before the last _enter()."""
+        if self._capturing():
+            torch.cuda.current_stream(self.device).wait_stream(self.stream)
+        else:
+            check(self._lib.mppi_release_stream(self.ctx, self._current()))
         return t
 
     def _empty(self, shape, dtype=torch.float32) -> torch.Tensor:
-        with torch.cuda.stream(self.stream):
-            return torch.empty(shape, dtype=dtype, device=self.device)
+        return torch.empty(shape, dtype=dtype, device=self.device)
 
     def _dev(self, a, n: int) -> torch.Tensor:
         self._enter()
+        if (torch.is_tensor(a) and a.dtype == torch.float32 and a.is_contiguous()
+                and a.numel() == n and a.device == self._dev_exact):
+            return a.detach()
         t = torch.as_tensor(np.asarray(a, np.float32) if not torch.is_tensor(a) else a)
         with torch.cuda.stream(self.stream):
             t = t.to(device=self.device, dtype=torch.float32).contiguous().reshape(n)
@@ -196,7 +235,7 @@ class Controller:
     # -- packing ------------------------------------------------------------
     def _offsets(self, kind: int) -> np.ndarray:
         off = (C.c_int64 * (self.n_inst + 1))()
-        check(lib().mppi_offsets(self.ctx, kind, off))
+        check(self._lib.mppi_offsets(self.ctx, kind, off))
         return np.array(off[:], dtype=np.int64)
 
     def offsets(self, kind: int) -> np.ndarray:
@@ -210,58 +249,58 @@ class Controller:
     # -- state --------------------------------------------------------------
     def set_state(self, x0) -> None:
         t = self._dev(x0, int(self._off[_abi.PACKED_STATE][-1]))
-        check(lib().mppi_set_state(self.ctx, t.data_ptr()))
+        check(self._lib.mppi_set_state(self.ctx, t.data_ptr()))
         self._x0 = t  # alive until the enqueued copy has run (stream order)
 
     def set_controls(self, u) -> None:
         t = self._dev(u, int(self._off[_abi.PACKED_CONTROLS][-1]))
-        check(lib().mppi_set_controls(self.ctx, t.data_ptr()))
+        check(self._lib.mppi_set_controls(self.ctx, t.data_ptr()))
         self._u = t
 
     def set_iteration(self, iteration: int) -> None:
-        self._enter()
-        check(lib().mppi_set_iteration(self.ctx, int(iteration)))
+        self._own()
+        check(self._lib.mppi_set_iteration(self.ctx, int(iteration)))
 
     def shift(self, steps: int, fill: str = "hold") -> None:
         """MPC warm start: u[t] <- u[t + steps]; the tail holds the last
         control ("hold") or becomes zero ("zero")."""
-        self._enter()
-        check(lib().mppi_shift(self.ctx, int(steps),
+        self._own()
+        check(self._lib.mppi_shift(self.ctx, int(steps),
                                {"hold": _abi.SHIFT_HOLD, "zero": _abi.SHIFT_ZERO}[fill]))
 
     # -- the iteration ------------------------------------------------------
     def sample(self) -> None:
-        self._enter()
-        check(lib().mppi_sample(self.ctx))
+        self._own()
+        check(self._lib.mppi_sample(self.ctx))
 
     def rollout(self) -> None:
-        self._enter()
-        check(lib().mppi_rollout(self.ctx))
+        self._own()
+        check(self._lib.mppi_rollout(self.ctx))
 
     def set_costs(self, S) -> None:
         t = self._dev(S, int(self._off[_abi.PACKED_SAMPLES][-1]))
-        check(lib().mppi_set_costs(self.ctx, t.data_ptr()))
+        check(self._lib.mppi_set_costs(self.ctx, t.data_ptr()))
         self._S = t
 
     def update(self) -> None:
-        self._enter()
-        check(lib().mppi_update(self.ctx))
+        self._own()
+        check(self._lib.mppi_update(self.ctx))
 
     def iterate(self, num_iters: int = 1) -> None:
-        self._enter()
-        check(lib().mppi_iterate(self.ctx, int(num_iters)))
+        self._own()
+        check(self._lib.mppi_iterate(self.ctx, int(num_iters)))
 
     def controls(self) -> torch.Tensor:
         """U: [T, m] for one instance, packed [sum T*m] for a batch."""
-        n = int(self._off[_abi.PACKED_CONTROLS][-1])
-        U = self._empty(n)
-        check(lib().mppi_get_controls(self.ctx, U.data_ptr()))
-        return self._leave(U if self.batch else U.reshape(self.T, self.m))
+        U = self._empty(int(self._off[_abi.PACKED_CONTROLS][-1]))
+        self._enter()
+        check(self._lib.mppi_get_controls(self.ctx, U.data_ptr()))
+        return self._leave(U if self.batch else U.view(self.T, self.m))
 
     # -- launch shapes ------------------------------------------------------
     def tuning(self) -> dict:
         t = _abi.Tuning()
-        check(lib().mppi_get_tuning(self.ctx, C.byref(t)))
+        check(self._lib.mppi_get_tuning(self.ctx, C.byref(t)))
         return t.as_dict()
 
     def set_tuning(self, **shape) -> None:
@@ -269,13 +308,13 @@ class Controller:
         noise_calls, rollout_form, cost_waves, update_form, batch_form,
         adjoint_tiles); the others keep their values."""
         t = _abi.Tuning()
-        check(lib().mppi_get_tuning(self.ctx, C.byref(t)))
+        check(self._lib.mppi_get_tuning(self.ctx, C.byref(t)))
         for k, v in shape.items():
             if k not in t.as_dict():
                 raise KeyError(k)
             setattr(t, k, int(v))
         self._enter()
-        check(lib().mppi_set_tuning(self.ctx, C.byref(t)))
+        check(self._lib.mppi_set_tuning(self.ctx, C.byref(t)))
 
     def autotune(self, reps: int = 10, cache: str | None = None) -> dict:
         """Time the candidate launch shapes on this context and apply the
@@ -291,7 +330,7 @@ class Controller:
                 return {"key": key, "tuning": self.tuning(), "cached": True}
         buf = C.create_string_buffer(8192)
         self._enter()
-        check(lib().mppi_autotune(self.ctx, int(reps), buf, len(buf)))
+        check(self._lib.mppi_autotune(self.ctx, int(reps), buf, len(buf)))
         result = {"key": key, "tuning": self.tuning(), "cached": False,
                   "timings": _at.parse_report(buf.value.decode())}
         if cache is not None:
@@ -300,9 +339,9 @@ class Controller:
 
     # -- differentiation ----------------------------------------------------
     def theta_len(self) -> int:
-        n = lib().mppi_theta_len(self.ctx)
+        n = self._lib.mppi_theta_len(self.ctx)
         if n == 0:
-            raise _abi.MPPIError(_abi.MPPI_ESTATE, lib().mppi_last_error().decode())
+            raise _abi.MPPIError(_abi.MPPI_ESTATE, self._lib.mppi_last_error().decode())
         return int(n)
 
     def theta(self) -> torch.Tensor:
@@ -321,23 +360,23 @@ class Controller:
         if a.size != self.theta_len():
             raise ValueError(f"theta has {a.size} entries, the context needs {self.theta_len()}")
         self._enter()
-        check(lib().mppi_set_theta(self.ctx, _fptr(a)))
+        check(self._lib.mppi_set_theta(self.ctx, _fptr(a)))
 
     def backward(self, dL_dU) -> torch.Tensor:
         """dL/dtheta of a loss on the controls of the last update."""
-        g = self._dev(dL_dU, self.T * self.m)
         out = self._empty(self.theta_len())
-        check(lib().mppi_backward(self.ctx, g.data_ptr(), out.data_ptr()))
+        g = self._dev(dL_dU, self.T * self.m)
+        check(self._lib.mppi_backward(self.ctx, g.data_ptr(), out.data_ptr()))
         self._g = g
         return self._leave(out)
 
     def backward_iters(self, dL_dU):
         """(dL/dtheta, dL/du0) through every update since the tape started
         (the last set_state / set_controls / set_theta / shift)."""
-        g = self._dev(dL_dU, self.T * self.m)
         out = self._empty(self.theta_len())
         du0 = self._empty(self.T * self.m)
-        check(lib().mppi_backward_iters(self.ctx, g.data_ptr(), out.data_ptr(), du0.data_ptr()))
+        g = self._dev(dL_dU, self.T * self.m)
+        check(self._lib.mppi_backward_iters(self.ctx, g.data_ptr(), out.data_ptr(), du0.data_ptr()))
         self._g = g
         return self._leave(out), self._leave(du0).reshape(self.T, self.m)
 
@@ -345,29 +384,34 @@ class Controller:
     def noise(self) -> torch.Tensor:
         n = int(self._off[_abi.PACKED_NOISE][-1])
         out = self._empty(n)
-        check(lib().mppi_get_debug(self.ctx, _abi.DEBUG_NOISE, out.data_ptr()))
+        self._enter()
+        check(self._lib.mppi_get_debug(self.ctx, _abi.DEBUG_NOISE, out.data_ptr()))
         return self._leave(out if self.batch else out.reshape(self.T, self.m, self.K))
 
     def costs(self) -> torch.Tensor:
         out = self._empty(int(self._off[_abi.PACKED_SAMPLES][-1]))
-        check(lib().mppi_get_debug(self.ctx, _abi.DEBUG_COSTS, out.data_ptr()))
+        self._enter()
+        check(self._lib.mppi_get_debug(self.ctx, _abi.DEBUG_COSTS, out.data_ptr()))
         return self._leave(out)
 
     def weights(self) -> torch.Tensor:
         out = self._empty(int(self._off[_abi.PACKED_SAMPLES][-1]))
-        check(lib().mppi_get_debug(self.ctx, _abi.DEBUG_WEIGHTS, out.data_ptr()))
+        self._enter()
+        check(self._lib.mppi_get_debug(self.ctx, _abi.DEBUG_WEIGHTS, out.data_ptr()))
         return self._leave(out)
 
     def crashes(self) -> torch.Tensor:
         out = self._empty(int(self._off[_abi.PACKED_SAMPLES][-1]), dtype=torch.int32)
-        check(lib().mppi_get_debug(self.ctx, _abi.DEBUG_CRASHES, out.data_ptr()))
+        self._enter()
+        check(self._lib.mppi_get_debug(self.ctx, _abi.DEBUG_CRASHES, out.data_ptr()))
         return self._leave(out)
 
     def stats(self):
         """dict (one instance) or list of dicts (batch): rho, eta, free energy,
         effective sample size, status word, iteration word."""
         raw = self._empty(8 * self.n_inst)
-        check(lib().mppi_get_debug(self.ctx, _abi.DEBUG_STATS, raw.data_ptr()))
+        self._enter()
+        check(self._lib.mppi_get_debug(self.ctx, _abi.DEBUG_STATS, raw.data_ptr()))
         self.stream.synchronize()
         f = raw.cpu().numpy().reshape(self.n_inst, 8)
         i = f.view(np.int32)
@@ -382,7 +426,7 @@ class Controller:
     def close(self) -> None:
         if getattr(self, "ctx", None):
             self.stream.synchronize()
-            lib().mppi_destroy(self.ctx)
+            self._lib.mppi_destroy(self.ctx)
             self.ctx = None
 
     def __del__(self):

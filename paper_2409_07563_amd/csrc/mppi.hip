@@ -650,7 +650,14 @@ struct mppi_ctx {
   // whether its noise was drawn ahead)
   std::map<int64_t, hipGraphExec_t> graphs;
   mppi_tuning tune{};                     // launch shapes (lanes: instance 0's choice)
-  ~mppi_ctx() { drop_graphs(); }
+  // ordering with the caller's streams (mppi_wait_stream, mppi_release_stream):
+  // events made on first use
+  hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  ~mppi_ctx() {
+    drop_graphs();
+    if (ev_in) (void)hipEventDestroy(ev_in);
+    if (ev_out) (void)hipEventDestroy(ev_out);
+  }
   void drop_graphs() {
     for (auto& g : graphs) (void)hipGraphExecDestroy(g.second);
     graphs.clear();
@@ -665,6 +672,15 @@ hipError_t tape_reset(mppi_ctx* c) {
   if (c->batch || !c->one().grad) return hipSuccess;
   c->tape_external = false;
   return launch_tape_reset(c->one().at<int32_t>(c->one().L.tape_count), c->stream);
+}
+
+// `after` waits (on the GPU) for what `before` holds now.
+hipError_t order_streams(hipEvent_t* ev, hipStream_t before, hipStream_t after) {
+  if (before == after) return hipSuccess;
+  hipError_t e = hipSuccess;
+  if (!*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(*ev, before);
+  return e == hipSuccess ? hipStreamWaitEvent(after, *ev, 0) : e;
 }
 
 // The single-pass update exists for single, non-gradient contexts with up to
@@ -1853,6 +1869,18 @@ mppi_status mppi_get_controls(mppi_ctx* c, float* d_U) {
   if (!c || !d_U) return fail(MPPI_EINVAL, "ctx and d_U must not be NULL");
   HIP_TRY(hipMemcpyAsync(d_U, c->ws + c->C.u, sizeof(float) * c->n_u, hipMemcpyDeviceToDevice,
                          c->stream));
+  return MPPI_OK;
+}
+
+mppi_status mppi_wait_stream(mppi_ctx* c, void* hip_stream) {
+  if (!c) return fail(MPPI_EINVAL, "ctx must not be NULL");
+  HIP_TRY(order_streams(&c->ev_in, static_cast<hipStream_t>(hip_stream), c->stream));
+  return MPPI_OK;
+}
+
+mppi_status mppi_release_stream(mppi_ctx* c, void* hip_stream) {
+  if (!c) return fail(MPPI_EINVAL, "ctx must not be NULL");
+  HIP_TRY(order_streams(&c->ev_out, c->stream, static_cast<hipStream_t>(hip_stream)));
   return MPPI_OK;
 }
 
