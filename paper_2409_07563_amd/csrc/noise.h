@@ -32,6 +32,19 @@ namespace noise {
 
 struct Words { uint32_t x0, x1, x2, x3; };
 
+// a ^ b ^ c, (a & b) | c and a with the sign flipped by bit 31 of b, one
+// operation each (v_bitop3_b32)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0xEA);
+}
+__device__ __forceinline__ float flip_sign(float a, uint32_t b) {
+  return __uint_as_float(
+      __builtin_amdgcn_bitop3_b32(__float_as_uint(a), b, 0x80000000u, 0x78));
+}
+
 __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2,
                                                uint32_t c3, uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -41,8 +54,12 @@ __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c2;
     const uint32_t lo0 = static_cast<uint32_t>(p0), hi0 = static_cast<uint32_t>(p0 >> 32);
     const uint32_t lo1 = static_cast<uint32_t>(p1), hi1 = static_cast<uint32_t>(p1 >> 32);
-    const uint32_t n0 = hi1 ^ c1 ^ k0;
-    const uint32_t n2 = hi0 ^ c3 ^ k1;
+    // The call index, the iteration and the instance are the same in every
+    // lane of most callers, so up to round 3 some of these words are scalar
+    // and stay in plain xors (the scalar unit's); from there on all operands
+    // differ by lane and one three-input operation forms each word.
+    const uint32_t n0 = r >= 3 ? xor3(hi1, c1, k0) : hi1 ^ c1 ^ k0;
+    const uint32_t n2 = r >= 4 ? xor3(hi0, c3, k1) : hi0 ^ c3 ^ k1;
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
     k0 += 0x9E3779B9u;  // the bump after the last round is never used
     k1 += 0xBB67AE85u;
@@ -64,26 +81,37 @@ __constant__ static const float kCos[6] = {0x1.000000p+0f, -0x1.3bd3ccp+4f, 0x1.
 __device__ __forceinline__ float radius(uint32_t j1) {
 #pragma clang fp contract(off)
   const uint32_t b = __float_as_uint(static_cast<float>(j1));  // exact conversion
-  const uint32_t mant = b & 0x7FFFFFu;
-  const bool high = mant > 0x3504F3u;                          // f > RN(sqrt 2)
-  // f in [sqrt(1/2), sqrt(2)): the mantissa with exponent 0, or -1 when high
-  const float f = __uint_as_float(mant | (high ? 0x3F000000u : 0x3F800000u));
-  const int e = static_cast<int>(b >> 23) - 127 + (high ? 1 : 0);
+  // f in [sqrt(1/2), sqrt(2)), f > RN(sqrt 2) belonging to the next exponent:
+  // taking the bits of RN(sqrt 2) and one more off b leaves that exponent in
+  // the high bits (less 150 = the bias, -1 and the 24 of 2^-24) and f's
+  // distance from the interval's lower end in the low 23
+  const uint32_t d = b - 0x3504F4u - (150u << 23);
+  const float ke = static_cast<float>(static_cast<int32_t>(d) >> 23);
+  const float f = __uint_as_float((d & 0x7FFFFFu) + (0x3504F4u + 0x3F000000u));
   const float x = f - 1.0f;
   float p = kLog[9];
 #pragma unroll
   for (int i = 8; i >= 0; --i) p = __builtin_fmaf(p, x, kLog[i]);
-  const float ke = static_cast<float>(e - 24);
   const float lnu = __builtin_fmaf(ke, 0x1.62e400p-1f, __builtin_fmaf(ke, 0x1.7f7d1cp-20f, x * p));
-  return __builtin_sqrtf(-2.0f * lnu);
+  // The square root of v in {-0} and [2^-23, 33.3], correctly rounded: from the
+  // hardware's reciprocal root (bounded, for v = -0), one Newton step on the
+  // residual v - s^2, which the fma forms exactly; all 2^24 arguments agree
+  // with the correctly rounded root.  A general sqrt also scales its argument
+  // and tries both neighbours: 16 operations, here 6.
+  const float v = -2.0f * lnu;
+  const float y = __builtin_fminf(__builtin_amdgcn_rsqf(__builtin_fabsf(v)), 0x1p+24f);
+  const float s = v * y;
+  return __builtin_fmaf(__builtin_fmaf(-s, s, v), 0.5f * y, s);
 }
 
-// (cos, sin)(2 pi j2 2^-24), j2 in [0, 2^24)
-__device__ __forceinline__ void angle(uint32_t j2, float& c_out, float& s_out) {
+// (cos, sin)(2 pi w 2^-32) for the high 24 bits of w, w = j2 2^8
+__device__ __forceinline__ void angle_word(uint32_t w, float& c_out, float& s_out) {
 #pragma clang fp contract(off)
-  const uint32_t q = (j2 + (1u << 21)) >> 22;
-  const int32_t rem = static_cast<int32_t>(j2) - static_cast<int32_t>(q << 22);
-  const float f = static_cast<float>(rem) * 0x1p-24f;
+  // bits 30 and 31 of q are the quadrant, the 22 bits below them (of the 24
+  // that count) the remainder plus 2^21; as the mantissa of a float in
+  // [1/4, 1/2) those are 3/8 + remainder 2^-24, and the difference is exact
+  const uint32_t q = w + (1u << 29);
+  const float f = __uint_as_float(and_or(q >> 7, 0x7FFFFEu, 0x3E800000u)) - 0.375f;
   const float y = f * f;
   float ps = kSin[4];
 #pragma unroll
@@ -92,12 +120,15 @@ __device__ __forceinline__ void angle(uint32_t j2, float& c_out, float& s_out) {
   float c = kCos[5];
 #pragma unroll
   for (int i = 4; i >= 0; --i) c = __builtin_fmaf(c, y, kCos[i]);
-  // rotate by q * pi/2: (c, s) -> (-s, c) per quadrant
-  const uint32_t qq = q & 3u;
-  const float cs = (qq & 1u) ? s : c;
-  const float sn = (qq & 1u) ? c : s;
-  c_out = ((qq + 1u) & 2u) ? -cs : cs;  // negated in quadrants 1 and 2
-  s_out = (qq & 2u) ? -sn : sn;         // negated in quadrants 2 and 3
+  // rotate by the quadrant: (c, s) -> (-s, c) per quarter turn
+  const bool odd = (q & (1u << 30)) != 0;
+  const float cs = odd ? s : c;
+  const float sn = odd ? c : s;
+  c_out = flip_sign(cs, q + (1u << 30));  // negated in quadrants 1 and 2
+  s_out = flip_sign(sn, q);               // negated in quadrants 2 and 3
+}
+__device__ __forceinline__ void angle(uint32_t j2, float& c_out, float& s_out) {
+  angle_word(j2 << 8, c_out, s_out);
 }
 
 // The two standard normals of one Box-Muller pair of Philox words.
@@ -105,7 +136,7 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, float& z0, fl
 #pragma clang fp contract(off)
   const float r = radius((a >> 8) + 1u);
   float c, s;
-  angle(b >> 8, c, s);
+  angle_word(b, c, s);
   z0 = r * c;
   z1 = r * s;
 }
@@ -141,11 +172,17 @@ __device__ __forceinline__ void emit_call(uint32_t key0, uint32_t key1, uint32_t
     }
   }
 #pragma unroll
+  for (int s = 0; s < 4; ++s) z[s] = sg[s] * z[s];
+  // only the wave that holds the mean sample takes the select
+  if (__builtin_expect(__ballot(zero) != 0, 0)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) z[s] = zero ? 0.0f : z[s];
+  }
+#pragma unroll
   for (int s = 0; s < 4; ++s) {
     const int n = n0 + s;
-    const float v = zero ? 0.0f : sg[s] * z[s];
-    if (n < TM) eps[static_cast<int64_t>(n) * ldk + k] = v;
-    if (out) out[s] = v;
+    if (n < TM) eps[static_cast<int64_t>(n) * ldk + k] = z[s];
+    if (out) out[s] = z[s];
   }
 }
 
