@@ -141,25 +141,11 @@ __device__ __forceinline__ void box_muller(uint32_t a, uint32_t b, float& z0, fl
   z1 = r * s;
 }
 
-// Philox call c of sample k: the four normals n = 4c .. 4c+3 (n = t*m + j),
-// scaled by sigma_j (or sigma_t[n] when a per-step table is given) and stored
-// at eps[n * ldk + k] (n < TM); zero for every n when `zero` (the noiseless
-// mean sample).  out (optional): the four values as stored (entries n >= TM
-// are computed but not stored).
-__device__ __forceinline__ void emit_call(uint32_t key0, uint32_t key1, uint32_t iteration,
-                                          uint32_t instance, int k, int c, int TM, int m,
-                                          const float* sigma, float* __restrict__ eps,
-                                          int64_t ldk, const float* __restrict__ sigma_t = nullptr,
-                                          bool zero = false, float* out = nullptr) {
-  const Words w = philox4x32_10(static_cast<uint32_t>(c), static_cast<uint32_t>(k), iteration,
-                                instance, key0, key1);
-  float z[4];
-  box_muller(w.x0, w.x1, z[0], z[1]);
-  box_muller(w.x2, w.x3, z[2], z[3]);
+// The four deviations of Philox call c (the per-step table is padded to a
+// multiple of four entries, so one aligned 16-byte read covers them).
+__device__ __forceinline__ void call_sigma(int c, int m, const float* sigma,
+                                           const float* __restrict__ sigma_t, float (&sg)[4]) {
   const int n0 = 4 * c;
-  // the four deviations of this call (the per-step table is padded to a
-  // multiple of four entries, so one aligned 16-byte read covers them)
-  float sg[4];
   if (sigma_t) {
     const float4 s4 = *reinterpret_cast<const float4*>(sigma_t + n0);
     sg[0] = s4.x; sg[1] = s4.y; sg[2] = s4.z; sg[3] = s4.w;
@@ -171,6 +157,18 @@ __device__ __forceinline__ void emit_call(uint32_t key0, uint32_t key1, uint32_t
       j = (j + 1 == m) ? 0 : j + 1;
     }
   }
+}
+
+// Philox call c of sample k: the four normals n = 4c .. 4c+3 (n = t*m + j)
+// times their deviations; zero for every n when `zero` (the noiseless mean
+// sample).
+__device__ __forceinline__ void draw_call(uint32_t key0, uint32_t key1, uint32_t iteration,
+                                          uint32_t instance, int k, int c, const float (&sg)[4],
+                                          bool zero, float (&z)[4]) {
+  const Words w = philox4x32_10(static_cast<uint32_t>(c), static_cast<uint32_t>(k), iteration,
+                                instance, key0, key1);
+  box_muller(w.x0, w.x1, z[0], z[1]);
+  box_muller(w.x2, w.x3, z[2], z[3]);
 #pragma unroll
   for (int s = 0; s < 4; ++s) z[s] = sg[s] * z[s];
   // only the wave that holds the mean sample takes the select
@@ -178,11 +176,52 @@ __device__ __forceinline__ void emit_call(uint32_t key0, uint32_t key1, uint32_t
 #pragma unroll
     for (int s = 0; s < 4; ++s) z[s] = zero ? 0.0f : z[s];
   }
+}
+
+// Philox call c of sample k, stored at eps[n * ldk + k] (n < TM).  out
+// (optional): the four values as stored (entries n >= TM are computed but not
+// stored).
+__device__ __forceinline__ void emit_call(uint32_t key0, uint32_t key1, uint32_t iteration,
+                                          uint32_t instance, int k, int c, int TM, int m,
+                                          const float* sigma, float* __restrict__ eps,
+                                          int64_t ldk, const float* __restrict__ sigma_t = nullptr,
+                                          bool zero = false, float* out = nullptr) {
+  float sg[4], z[4];
+  call_sigma(c, m, sigma, sigma_t, sg);
+  draw_call(key0, key1, iteration, instance, k, c, sg, zero, z);
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    const int n = n0 + s;
+    const int n = 4 * c + s;
     if (n < TM) eps[static_cast<int64_t>(n) * ldk + k] = z[s];
     if (out) out[s] = z[s];
+  }
+}
+
+// Philox call c of the samples k .. k + 3 (those below K), stored with one
+// 16-byte store per row: k and ldk multiples of four, eps aligned to 16
+// bytes.  zero: sample k is the mean sample.
+__device__ __forceinline__ void emit_call4(uint32_t key0, uint32_t key1, uint32_t iteration,
+                                           uint32_t instance, int k, int K, int c, int TM, int m,
+                                           const float* sigma, float* __restrict__ eps,
+                                           int64_t ldk, const float* __restrict__ sigma_t,
+                                           bool zero) {
+  float sg[4], z[4][4];
+  call_sigma(c, m, sigma, sigma_t, sg);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    draw_call(key0, key1, iteration, instance, k + i, c, sg, zero && i == 0, z[i]);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int n = 4 * c + s;
+    if (n >= TM) continue;
+    float* row = eps + static_cast<int64_t>(n) * ldk + k;
+    if (k + 4 <= K) {
+      *reinterpret_cast<float4*>(row) = float4{z[0][s], z[1][s], z[2][s], z[3][s]};
+    } else {
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        if (k + i < K) row[i] = z[i][s];
+    }
   }
 }
 

@@ -5,16 +5,22 @@
 // samples, so each of the four stores of a wave is one contiguous 256-byte
 // row segment of the [T*m][ldk] layout (k fastest).  The kernel is VALU-bound
 // (Philox + two Box-Muller pairs, ~35 VALU operations per normal) rather than
-// bound by its HBM writes.  The range reductions, the root and the quadrant
-// are written for the operation count (noise.h); with the plain forms it was
-// ~50, and a batch of 256 instances (1.6 M samples, T 50 .. 200) took 428 us
-// instead of 347.
+// bound by its HBM writes.
+//
+// Large draws take four samples per thread: with one, a wave lives for one
+// call, about 150 operations, behind a chain of scalar loads (arguments,
+// iteration word, deviations); four samples pay that once, and their rows are
+// stored 16 bytes a lane.  One and four samples per thread: K 65536, T 200,
+// m 4 66 and 46 us (the stores alone take 31, the arithmetic alone 40);
+// K 32768, T 200, m 2 20 and 16 us.
 #include "common.h"
 #include "noise.h"
 
 namespace mppi {
 
-// calls: Philox calls per thread (the calls blockIdx.y * calls + i).
+// FOUR: four samples per thread; calls: Philox calls per thread and sample
+// (the calls blockIdx.y * calls + i).
+template <bool FOUR>
 __global__ __launch_bounds__(256) void noise_kernel(uint32_t key0, uint32_t key1,
                                                     const uint32_t* __restrict__ d_iteration,
                                                     uint32_t iteration, uint32_t instance,
@@ -22,16 +28,27 @@ __global__ __launch_bounds__(256) void noise_kernel(uint32_t key0, uint32_t key1
                                                     float* __restrict__ eps, int64_t ldk,
                                                     int calls, const float* __restrict__ sigma_t,
                                                     int mean_sample, uint32_t* d_word_out) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  const int k = (blockIdx.x * blockDim.x + threadIdx.x) * (FOUR ? 4 : 1);
   if (k >= K) return;
   const uint32_t it = d_iteration ? *d_iteration + iteration : iteration;
   if (d_word_out && k == 0 && blockIdx.y == 0) *d_word_out = it;
   const int ncall = (TM + 3) / 4;
   const int c0 = blockIdx.y * calls;
-  for (int c = c0; c < c0 + calls && c < ncall; ++c)
-    noise::emit_call(key0, key1, it, instance, k, c, TM, m, sigma.v, eps, ldk, sigma_t,
-                     mean_sample && k == 0);
+  const bool zero = mean_sample && k == 0;
+  for (int c = c0; c < c0 + calls && c < ncall; ++c) {
+    if constexpr (FOUR)
+      noise::emit_call4(key0, key1, it, instance, k, K, c, TM, m, sigma.v, eps, ldk, sigma_t,
+                        zero);
+    else
+      noise::emit_call(key0, key1, it, instance, k, c, TM, m, sigma.v, eps, ldk, sigma_t, zero);
+  }
 }
+
+// Four samples per thread from this many Philox calls in all (four waves per
+// SIMD then, on 256 CUs: 9.6 us with one sample per thread, 8.3 with four;
+// below, too few waves are left to cover the loads), where the rows can be
+// stored 16 bytes a lane.
+constexpr int64_t kFourMinCalls = int64_t{1} << 20;
 
 hipError_t launch_noise(uint64_t seed, const uint32_t* d_iteration, uint32_t iteration,
                         uint32_t instance, int K, int T, int m, const float* sigma,
@@ -42,10 +59,14 @@ hipError_t launch_noise(uint64_t seed, const uint32_t* d_iteration, uint32_t ite
   const int ncall = (TM + 3) / 4;
   Sigma8 s{};
   for (int j = 0; j < m; ++j) s.v[j] = sigma[j];
-  dim3 grid((K + 255) / 256, (ncall + calls - 1) / calls);
-  hipLaunchKernelGGL(noise_kernel, grid, dim3(256), 0, stream, static_cast<uint32_t>(seed),
-                     static_cast<uint32_t>(seed >> 32), d_iteration, iteration, instance, K,
-                     TM, m, s, d_eps, ldk, calls, d_sigma_t, mean_sample ? 1 : 0, d_word_out);
+  const bool four = static_cast<int64_t>(K) * ncall >= kFourMinCalls && ldk % 4 == 0 &&
+                    reinterpret_cast<uintptr_t>(d_eps) % sizeof(float4) == 0;
+  const int per = four ? 1024 : 256;  // samples per workgroup
+  dim3 grid((K + per - 1) / per, (ncall + calls - 1) / calls);
+  hipLaunchKernelGGL(four ? noise_kernel<true> : noise_kernel<false>, grid, dim3(256), 0, stream,
+                     static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), d_iteration,
+                     iteration, instance, K, TM, m, s, d_eps, ldk, calls, d_sigma_t,
+                     mean_sample ? 1 : 0, d_word_out);
   return hipGetLastError();
 }
 
