@@ -310,7 +310,12 @@ mppi_status mppi_offsets(const mppi_ctx* ctx, int32_t what, int64_t* host_offset
  * parallel.  It exists for single contexts with BICYCLE dynamics, RK4 and
  * T <= 256 (not for gradient mode), with lanes_per_sample 16 and
  * rollout_block threads per workgroup.  Equally accurate: the positions are
- * summed with compensation; only the rounding order differs. */
+ * summed with compensation; only the rounding order differs.
+ * Until mppi_set_tuning or mppi_autotune is called, a context for which the
+ * form exists and neither MPPI_F_ROLLOUT_LANE nor _QUAD is set also runs it
+ * (16 or 32 lanes, 256 threads) where it is the faster one: all but short
+ * horizons with many samples.  mppi_get_tuning then reports the fused form
+ * that these calls start from; setting it, even unchanged, selects it. */
 enum { MPPI_ROLLOUT_FUSED = 0, MPPI_ROLLOUT_SPLIT = 1, MPPI_ROLLOUT_SCAN = 2 };
 /* Steps (a3)-(a6) (Algorithm 1, Eq. mppi_update_rule):
  *  TWO_PASS: a weights step in one workgroup writes the weights, then one

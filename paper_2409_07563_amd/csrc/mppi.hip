@@ -650,6 +650,7 @@ struct mppi_ctx {
   // whether its noise was drawn ahead)
   std::map<int64_t, hipGraphExec_t> graphs;
   mppi_tuning tune{};                     // launch shapes (lanes: instance 0's choice)
+  bool tuned = false;                     // mppi_set_tuning or mppi_autotune chose them
   // ordering with the caller's streams (mppi_wait_stream, mppi_release_stream):
   // events made on first use
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -1133,6 +1134,30 @@ bool rollout_draws_noise(const mppi_ctx* c) {
   return !c->batch && !(I.hidden || I.grad) && c->tune.rollout_form != MPPI_ROLLOUT_SPLIT;
 }
 
+// Lanes per sample of the time-parallel rollout (256 threads per workgroup) of
+// a context whose launch shapes nobody has chosen, 0 where the grouped or
+// one-lane rollout is the faster one.  Time-parallel, a step's arithmetic is
+// the same but the chain is T / 16 or T / 32 steps instead of T; it loses only
+// where the samples alone fill the chip and the horizon is too short to pay
+// for the prefix sums.  Rollout, us, circles cost (grouped or one-lane | 16
+// lanes | 32 lanes):
+//   T  30: K 512 11.5 | 6.6 | 5.4, K 32768 15.6 | 14.7 | 22.0, K 65536 21.1 | 24.2 | 39.3
+//   T 100: K 512 25.9 | 10.2 | 7.5, K 8192 28.5 | 12.1 | 12.2, K 65536 58.3 | 43.3 | 55.5
+//   T 200: K 3001 50.2 | 16.1 | 13.3, K 8192 54.7 | 20.2 | 21.1, K 65536 113.7 | 76.6 | 104.1
+// Where the lines lie (grouped or one-lane | time-parallel, circles; costmap):
+//   T  8: K  8192  6.8 |  6.0;  9.4 |  6.9    K 16384  6.9 |  8.0;  9.5 |  9.3
+//   T 16: K 16384  8.7 |  8.2; 11.5 |  9.5    K 32768 10.6 | 12.4; 23.6 | 14.5
+//   T 24: K 32768 13.4 | 14.0; 29.3 | 17.3    T 48: K 65536 32.0 | 27.0; 36.9 | 36.4
+// and 32 lanes while 16 lanes leave SIMDs idle (T 30, K 3001: 5.9 with 16
+// lanes, 6.5 with 32; T 77, K 3001: 8.8 and 8.2).
+int default_scan_lanes(const Instance& I) {
+  if (I.hidden || I.grad || (I.cfg.flags & (MPPI_F_ROLLOUT_LANE | MPPI_F_ROLLOUT_QUAD))) return 0;
+  const int lanes = I.K <= 1024 || (I.K <= 4096 && I.T > 64) ? 32 : 16;
+  if (!rollout_scan_supported(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, I.T, lanes)) return 0;
+  const int min_steps = I.K > 32768 ? 48 : I.K > 16384 ? 24 : I.K > 8192 ? 16 : 1;
+  return I.T >= min_steps ? lanes : 0;
+}
+
 // next: also draw the next iteration's noise (rollout_draws_noise only).
 hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
   const Instance& I = c->one();
@@ -1160,11 +1185,14 @@ hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
                                 c->tune.rollout_block, c->tune.cost_waves);
   NoiseJob job{};
   if (next) job = next_noise_job(c);
-  if (c->tune.rollout_form == MPPI_ROLLOUT_SCAN)
+  const int scan = c->tuned ? (c->tune.rollout_form == MPPI_ROLLOUT_SCAN
+                                   ? c->tune.lanes_per_sample : 0)
+                            : default_scan_lanes(I);
+  if (scan)
     return launch_rollout_scan(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.dp, I.x0,
                                I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
-                               c->stream, c->tune.rollout_block, next ? &job : nullptr,
-                               c->tune.lanes_per_sample);
+                               c->stream, c->tuned ? c->tune.rollout_block : 256,
+                               next ? &job : nullptr, scan);
   return launch_rollout(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.lanes, I.dp, I.x0,
                         I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
                         c->stream, c->tune.rollout_block, next ? &job : nullptr);
@@ -1474,6 +1502,7 @@ mppi_status mppi_set_tuning(mppi_ctx* c, const mppi_tuning* t) {
   }
   if (!(I.hidden || I.grad)) I.lanes = t->lanes_per_sample;
   c->tune = *t;
+  c->tuned = true;
   c->drop_graphs();
   return MPPI_OK;
 }
