@@ -1158,6 +1158,20 @@ int default_scan_lanes(const Instance& I) {
   return I.T >= min_steps ? lanes : 0;
 }
 
+// Threads per workgroup of the fused rollout of a context whose launch shapes
+// nobody has chosen: with 64 the dispatcher puts waves on SIMDs that hold one
+// while others are empty, with 256 every CU's four SIMDs get one each.  One
+// iteration, 64 | 256 threads, us: quadrotor K 65536 T 200 271 | 236, K 32768
+// T 200 196 | 190, K 10007 T 200 147 | 145; double integrator K 65536 T 200
+// 99 | 97; bicycle (one lane) K 65536 T 30 47 | 42.  Below, for the shorter
+// steps, one wave per CU is the better: double integrator K 16384 T 100 17.4
+// and 19.1 for the rollout.
+int default_rollout_block(const mppi_ctx* c) {
+  const Instance& I = c->one();
+  if (I.lanes == 1 && (I.K >= 32768 || I.cfg.dynamics == MPPI_DYN_QUADROTOR)) return 256;
+  return c->tune.rollout_block;
+}
+
 // next: also draw the next iteration's noise (rollout_draws_noise only).
 hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
   const Instance& I = c->one();
@@ -1195,7 +1209,8 @@ hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
                                next ? &job : nullptr, scan);
   return launch_rollout(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.lanes, I.dp, I.x0,
                         I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
-                        c->stream, c->tune.rollout_block, next ? &job : nullptr);
+                        c->stream, c->tuned ? c->tune.rollout_block : default_rollout_block(c),
+                        next ? &job : nullptr);
 }
 
 // next: the weights launch also draws the next iteration's noise into the
