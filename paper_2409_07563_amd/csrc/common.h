@@ -92,10 +92,27 @@ struct NoiseJob {
   int kblocks;
 };
 
+// The 8 XCDs take workgroups in turn and have an L2 each.  The noise is dealt to
+// them by groups of 256 samples, group g to XCD g mod 8, and a rollout whose
+// workgroups follow finds its noise in its own L2.
+constexpr int kXcds = 8, kGroupSamples = 256;
+// sample groups, filled up to a multiple of the XCDs (empty groups do nothing)
+inline int padded_groups(int K) {
+  return (K + kXcds * kGroupSamples - 1) / (kXcds * kGroupSamples) * kXcds;
+}
+// Workgroup b of a launch with `per` workgroups per group, as group * per + its
+// number in the group: group g runs on XCD g mod 8.
+__device__ __forceinline__ int grouped_index(int b, int per) {
+  const int i = b / kXcds;
+  return (i / per * kXcds + b % kXcds) * per + i % per;
+}
+
 // Workgroups of `threads` threads that draw a NoiseJob: kblocks sample blocks
 // times the Philox call groups (fills job->kblocks).
 inline int noise_job_blocks(NoiseJob* job, int threads) {
   job->kblocks = (job->K + threads - 1) / threads;
+  // 256 threads: group g of the samples to XCD g mod 8 whatever the call
+  if (threads == kGroupSamples) job->kblocks = padded_groups(job->K);
   const int ncall = (job->TM + 3) / 4;
   return job->kblocks * ((ncall + job->calls - 1) / job->calls);
 }

@@ -18,9 +18,12 @@
 
 namespace mppi {
 
-// FOUR: four samples per thread; calls: Philox calls per thread and sample
-// (the calls blockIdx.y * calls + i).
-template <bool FOUR>
+// FOUR: four samples per thread; calls: Philox calls per thread and sample.
+// A workgroup covers one group of 256 samples (grouped so that their rollout
+// finds them in its L2): one thread per sample, or (FOUR) 64 lanes of four
+// samples per wave, the waves taking different calls.  WIDE: 1024 samples of
+// the same calls.
+template <bool FOUR, bool WIDE>
 __global__ __launch_bounds__(256) void noise_kernel(uint32_t key0, uint32_t key1,
                                                     const uint32_t* __restrict__ d_iteration,
                                                     uint32_t iteration, uint32_t instance,
@@ -28,12 +31,16 @@ __global__ __launch_bounds__(256) void noise_kernel(uint32_t key0, uint32_t key1
                                                     float* __restrict__ eps, int64_t ldk,
                                                     int calls, const float* __restrict__ sigma_t,
                                                     int mean_sample, uint32_t* d_word_out) {
-  const int k = (blockIdx.x * blockDim.x + threadIdx.x) * (FOUR ? 4 : 1);
+  const int slice = blockIdx.y;
+  const int t = threadIdx.x;
+  const int k = WIDE ? (blockIdx.x * 256 + t) * 4
+                     : blockIdx.x * kGroupSamples + (FOUR ? t % kWave * 4 : t);
   if (k >= K) return;
   const uint32_t it = d_iteration ? *d_iteration + iteration : iteration;
-  if (d_word_out && k == 0 && blockIdx.y == 0) *d_word_out = it;
+  if (d_word_out && blockIdx.x == 0 && slice == 0 && t == 0) *d_word_out = it;
   const int ncall = (TM + 3) / 4;
-  const int c0 = blockIdx.y * calls;
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int c0 = (FOUR && !WIDE ? slice * 4 + wave : slice) * calls;
   const bool zero = mean_sample && k == 0;
   for (int c = c0; c < c0 + calls && c < ncall; ++c) {
     if constexpr (FOUR)
@@ -43,12 +50,20 @@ __global__ __launch_bounds__(256) void noise_kernel(uint32_t key0, uint32_t key1
       noise::emit_call(key0, key1, it, instance, k, c, TM, m, sigma.v, eps, ldk, sigma_t, zero);
   }
 }
+static_assert(kGroupSamples == 256 && kGroupSamples == 4 * kWave, "one group per workgroup");
 
 // Four samples per thread from this many Philox calls in all (four waves per
 // SIMD then, on 256 CUs: 9.6 us with one sample per thread, 8.3 with four;
 // below, too few waves are left to cover the loads), where the rows can be
 // stored 16 bytes a lane.
 constexpr int64_t kFourMinCalls = int64_t{1} << 20;
+// 1024 samples per workgroup from this many bytes of noise, of which the L2s
+// (32 MB) can keep little: whole rows are then written one after the other,
+// which the update's pass over the rows gains more from.  Sampling and rollout |
+// one iteration, us, quadrotor, 256 and 1024 samples per workgroup: K 32768
+// T 64 57 and 65 | 61 and 61; K 65536 T 64 65 and 71 | 74 and 75; K 65536 T 100
+// 93 and 99 | 117 and 115; K 65536 T 200 179 and 183 | 216 and 212.
+constexpr int64_t kWideMinBytes = int64_t{80} << 20;
 
 hipError_t launch_noise(uint64_t seed, const uint32_t* d_iteration, uint32_t iteration,
                         uint32_t instance, int K, int T, int m, const float* sigma,
@@ -61,9 +76,13 @@ hipError_t launch_noise(uint64_t seed, const uint32_t* d_iteration, uint32_t ite
   for (int j = 0; j < m; ++j) s.v[j] = sigma[j];
   const bool four = static_cast<int64_t>(K) * ncall >= kFourMinCalls && ldk % 4 == 0 &&
                     reinterpret_cast<uintptr_t>(d_eps) % sizeof(float4) == 0;
-  const int per = four ? 1024 : 256;  // samples per workgroup
-  dim3 grid((K + per - 1) / per, (ncall + calls - 1) / calls);
-  hipLaunchKernelGGL(four ? noise_kernel<true> : noise_kernel<false>, grid, dim3(256), 0, stream,
+  const bool wide = four && int64_t{4} * ldk * TM >= kWideMinBytes;
+  const int per = four && !wide ? 4 * calls : calls;  // calls per workgroup
+  const int ny = (ncall + per - 1) / per;
+  const auto kernel = wide ? noise_kernel<true, true>
+                           : four ? noise_kernel<true, false> : noise_kernel<false, false>;
+  hipLaunchKernelGGL(kernel, dim3(wide ? (K + 1023) / 1024 : padded_groups(K), ny), dim3(256), 0,
+                     stream,
                      static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32), d_iteration,
                      iteration, instance, K, TM, m, s, d_eps, ldk, calls, d_sigma_t,
                      mean_sample ? 1 : 0, d_word_out);

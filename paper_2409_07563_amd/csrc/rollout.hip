@@ -272,7 +272,8 @@ hipError_t launch_rollout(uint32_t dynamics, uint32_t integrator, uint32_t cost,
     if (e != hipSuccess) return e;
   }
   const int64_t threads = static_cast<int64_t>(K) * lanes_per_sample;
-  const int rblocks = static_cast<int>((threads + block - 1) / block);
+  int rblocks = static_cast<int>((threads + block - 1) / block);
+  if (next) rblocks = (rblocks + kXcds - 1) / kXcds * kXcds;  // the noise starts at XCD 0
   NoiseJob job{};
   int blocks = rblocks;
   if (next) {

@@ -133,7 +133,7 @@ template <class Cost, bool FAST, bool COUNT, int CMAX, int L>
 __global__ __launch_bounds__(kScanMaxBlock) void rollout_bicycle_scan_kernel(
     DevParams p, const float* __restrict__ x0, const float* __restrict__ u,
     const float* __restrict__ eps, int64_t ldk, int K, int T, int C, float* __restrict__ S,
-    int32_t* __restrict__ crashes, int rblocks, NoiseJob job) {
+    int32_t* __restrict__ crashes, int rblocks, int per, NoiseJob job) {
   if (static_cast<int>(blockIdx.x) >= rblocks) {  // the next iteration's noise
     next_noise(job, blockIdx.x - rblocks);
     return;
@@ -141,7 +141,8 @@ __global__ __launch_bounds__(kScanMaxBlock) void rollout_bicycle_scan_kernel(
   constexpr int N = 5, M = 2;
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * M, lds);
-  const int gl = blockIdx.x * blockDim.x + threadIdx.x;
+  const int b = per ? grouped_index(blockIdx.x, per) : blockIdx.x;
+  const int gl = b * blockDim.x + threadIdx.x;
   const int lane = gl & (L - 1);  // chunk of the horizon
   const int k = gl / L;
   if (k >= K) return;  // whole groups leave together; no barrier follows
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(kScanMaxBlock) void rollout_bicycle_scan_kernel(
 namespace {
 
 using ScanFn = void (*)(DevParams, const float*, const float*, const float*, int64_t, int, int,
-                        int, float*, int32_t*, int, NoiseJob);
+                        int, float*, int32_t*, int, int, NoiseJob);
 
 template <class Cost, bool FAST, int CMAX, int L>
 ScanFn pick_scan(bool count) {
@@ -382,8 +383,21 @@ hipError_t launch_rollout_scan(uint32_t dynamics, uint32_t integrator, uint32_t 
                                        static_cast<int>(lds));
     if (e != hipSuccess) return e;
   }
+  // A 16- or 32-lane workgroup reads 64 or 32 bytes of each noise row, so two to
+  // four neighbours share a 128-byte line: dealt by groups they share it in one
+  // L2, which holds what the noise launch wrote there.  Not for a handful of
+  // groups, which would fill the XCDs unevenly, nor where two noise buffers no
+  // longer fit in the L2s (4 MB each) with room to spare.  One iteration, us,
+  // without | with: T 100: K 512 10.7 | 10.8, K 3001 14.9 | 13.7, K 8192 22.0 |
+  // 20.3, K 9000 24.7 | 21.8, K 16384 28.5 | 30.8; T 200: K 3001 21.0 | 19.6,
+  // K 8192 30.0 | 32.0.
+  const int64_t noise_bytes = int64_t{4} * ldk * T * 2;
+  const bool grouped = K >= 2048 && noise_bytes <= int64_t{10} << 20;
+  const int per = grouped ? kGroupSamples * lanes / block : 0;
   const int64_t threads = static_cast<int64_t>(K) * lanes;
-  const int rblocks = static_cast<int>((threads + block - 1) / block);
+  int rblocks = static_cast<int>((threads + block - 1) / block);
+  if (grouped) rblocks = padded_groups(K) * per;
+  else if (next) rblocks = (rblocks + kXcds - 1) / kXcds * kXcds;  // the noise starts at XCD 0
   NoiseJob job{};
   int blocks = rblocks;
   if (next) {
@@ -391,7 +405,7 @@ hipError_t launch_rollout_scan(uint32_t dynamics, uint32_t integrator, uint32_t 
     blocks += noise_job_blocks(&job, block);
   }
   hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(block), lds, stream, p, d_x0,
-                     d_u, d_eps, ldk, K, T, C, d_S, d_crashes, rblocks, job);
+                     d_u, d_eps, ldk, K, T, C, d_S, d_crashes, rblocks, per, job);
   return hipGetLastError();
 }
 

@@ -70,3 +70,36 @@ def test_batch_noise_slices(mppi, oracle_lib, n, tile):
     for i, wl in enumerate(insts):
         o = oracle_lib.workload_noise(wl)
         assert np.array_equal(eps[i].view(np.uint32), o.ravel().view(np.uint32)), i
+
+
+# one launch's samples grouped for the XCDs or not: around both limits of the
+# rule (2048 samples, 10 MiB of noise), ragged, with one iteration's noise drawn
+# ahead by the launch before; T 257 has no time-parallel rollout
+@pytest.mark.parametrize("K,T", [(2047, 40), (2048, 40), (2049, 40), (6553, 200), (6561, 200),
+                                 (9000, 33), (300, 257)])
+def test_grouped_rollouts(mppi, oracle_lib, K, T):
+    wl = W.c2("circles", K=K, T=T, iters=1)
+    a, b = mppi.Controller(wl), mppi.Controller(wl)
+    a.iterate(3)
+    for _ in range(3):
+        b.sample()
+        eps, word = _np(b.noise()), b.stats()["iteration"]
+        b.rollout()
+        b.update()
+    o = oracle_lib.noise(wl.seed, word, wl.instance, K, T, wl.m, wl.sigma)
+    assert np.array_equal(eps.view(np.uint32), o.view(np.uint32))
+    for x, y in ((a.costs(), b.costs()), (a.controls(), b.controls())):
+        assert np.array_equal(_np(x).view(np.uint32), _np(y).view(np.uint32))
+    a.close()
+    b.close()
+
+
+@pytest.mark.parametrize("K,T", [(65536, 79), (65536, 80), (65530, 81)])
+def test_wide_noise(mppi, oracle_lib, K, T):
+    wl = W.c3(K=K, T=T)
+    ctl = mppi.Controller(wl)
+    ctl.sample()
+    eps = _np(ctl.noise())
+    ctl.close()
+    o = oracle_lib.workload_noise(wl)
+    assert np.array_equal(eps.view(np.uint32), o.view(np.uint32))
