@@ -118,8 +118,9 @@ enum {
                                 intrinsics for trigonometry, Sec. III-B) */
   MPPI_F_ROLLOUT_LANE = 4u,  /* force one lane per sample in the rollout */
   MPPI_F_ROLLOUT_QUAD = 8u,  /* force four lanes per sample (bicycle + RK4 only);
-                                by default the library picks four lanes per sample
-                                for the bicycle with RK4 when K <= 32768 */
+                                by default the time-parallel form or, where that is
+                                slower or does not exist, four lanes per sample when
+                                K <= 32768: see mppi_tuning) */
   MPPI_F_REQUIRES_GRAD = 16u, /* keep what mppi_backward needs: the rollout stores
                                 state checkpoints every params.checkpoint_every
                                 steps and a copy of the controls it used (BICYCLE
@@ -364,8 +365,8 @@ typedef struct mppi_tuning {
                                the faster form for the number of samples, the
                                largest in gradient mode) */
   int32_t batch_tile;       /* samples per work tile of a batch context: 64, 128 or 256 */
-  int32_t noise_calls;      /* Philox calls per thread of the single-instance noise
-                               kernel: 1, 2 or 4 */
+  int32_t noise_calls;      /* Philox calls per thread and sample of the
+                               single-instance noise kernel: 1, 2 or 4 */
   int32_t rollout_form;     /* MPPI_ROLLOUT_FUSED (default), MPPI_ROLLOUT_SPLIT or
                                MPPI_ROLLOUT_SCAN; in the split form
                                lanes_per_sample (1, or 4 for the bicycle with RK4)

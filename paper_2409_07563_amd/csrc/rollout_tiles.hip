@@ -108,9 +108,10 @@ __global__ __launch_bounds__(kWave) void rollout_tile_kernel(
 // length of the chain and the busiest SIMD bound the kernel: a binary32 MFMA
 // keeps its SIMD's vector unit from issuing, and the bicycle's and the cost's
 // arithmetic must not pile up on one SIMD.  Eight waves are launched for SW = 4
-// (two per SIMD), of which two stay besides the MLP's four; which two depends on
-// the workgroup, so that the helper waves of the two workgroups of a CU sit on
-// four different SIMDs.
+// (two per SIMD), of which two stay besides the MLP's four, on different SIMDs.
+// Which two alternates between workgroups i and i + 256, the pair that a CU
+// holds: where both start on the same SIMD their helpers sit on four.  The
+// hardware chooses where a workgroup starts, so that is not assured.
 // K = 8192, T = 100, us, against a form that repeated the bicycle step after the
 // MLP and handed the state back through a third barrier: H = 64 175 -> 137 (one
 // tile per CU, K = 4096: 126 -> 84), BF 111 -> 89; H = 32 140 -> 90, BF 98 -> 69.
