@@ -8,8 +8,10 @@ caller's tensor first orders that stream after torch's current stream, and
 every tensor a call returns is ordered back onto torch's current stream, so
 callers can ignore streams; the other calls (shift, sample, rollout, update,
 iterate, set_iteration) touch only the context's own memory and follow each other
-on its stream (while torch's current stream is under capture they are ordered
-after it too, which makes them part of the capture).
+on its stream.  While torch's current stream is under capture they are ordered
+after it too, which makes them part of the capture; a replay then runs them on
+the stream it is launched on, so from the first such call on every call of that
+controller is ordered after torch's current stream, and that stream after it.
 
 The ordering uses the library's two events (mppi_wait_stream,
 mppi_release_stream): a torch Stream.wait_stream makes a new event and costs 19 us
@@ -181,6 +183,7 @@ class Controller:
                                     C.byref(ctx)))
         self.ctx = ctx
         self._lib = L
+        self._joined = False  # a call of this controller is part of a captured graph
         # where a tensor has to live to be handed to the library as it is
         self._dev_exact = torch.empty(0, device=self.device).device
         self._off = {k: self._offsets(k) for k in (_abi.PACKED_STATE, _abi.PACKED_CONTROLS,
@@ -200,15 +203,22 @@ class Controller:
     def _enter(self) -> None:
         """Order the library's stream after torch's current stream."""
         if self._capturing():
+            self._joined = True
             self.stream.wait_stream(torch.cuda.current_stream(self.device))
         else:
             check(self._lib.mppi_wait_stream(self.ctx, self._current()))
 
     def _own(self) -> None:
         """Before a call that reads none of the caller's tensors: only a capture
-        of torch's current stream has to be joined."""
-        if self._capturing():
+        of torch's current stream has to be joined, and the replays of an earlier
+        one waited for."""
+        if self._joined or self._capturing():
             self._enter()
+
+    def _done(self) -> None:
+        """After such a call: a replay enqueued next starts after it."""
+        if self._joined and not self._capturing():
+            check(self._lib.mppi_release_stream(self.ctx, self._current()))
 
     def _leave(self, t: torch.Tensor) -> torch.Tensor:
         """Order torch's current stream after the library's work on t, which was
@@ -260,6 +270,7 @@ class Controller:
     def set_iteration(self, iteration: int) -> None:
         self._own()
         check(self._lib.mppi_set_iteration(self.ctx, int(iteration)))
+        self._done()
 
     def shift(self, steps: int, fill: str = "hold") -> None:
         """MPC warm start: u[t] <- u[t + steps]; the tail holds the last
@@ -267,15 +278,18 @@ class Controller:
         self._own()
         check(self._lib.mppi_shift(self.ctx, int(steps),
                                {"hold": _abi.SHIFT_HOLD, "zero": _abi.SHIFT_ZERO}[fill]))
+        self._done()
 
     # -- the iteration ------------------------------------------------------
     def sample(self) -> None:
         self._own()
         check(self._lib.mppi_sample(self.ctx))
+        self._done()
 
     def rollout(self) -> None:
         self._own()
         check(self._lib.mppi_rollout(self.ctx))
+        self._done()
 
     def set_costs(self, S) -> None:
         t = self._dev(S, int(self._off[_abi.PACKED_SAMPLES][-1]))
@@ -285,10 +299,12 @@ class Controller:
     def update(self) -> None:
         self._own()
         check(self._lib.mppi_update(self.ctx))
+        self._done()
 
     def iterate(self, num_iters: int = 1) -> None:
         self._own()
         check(self._lib.mppi_iterate(self.ctx, int(num_iters)))
+        self._done()
 
     def controls(self) -> torch.Tensor:
         """U: [T, m] for one instance, packed [sum T*m] for a batch."""
@@ -361,6 +377,7 @@ class Controller:
             raise ValueError(f"theta has {a.size} entries, the context needs {self.theta_len()}")
         self._enter()
         check(self._lib.mppi_set_theta(self.ctx, _fptr(a)))
+        self._done()
 
     def backward(self, dL_dU) -> torch.Tensor:
         """dL/dtheta of a loss on the controls of the last update."""
@@ -425,6 +442,8 @@ class Controller:
 
     def close(self) -> None:
         if getattr(self, "ctx", None):
+            if self._joined and not self._capturing():
+                self._enter()  # replays still running use the workspace
             self.stream.synchronize()
             self._lib.mppi_destroy(self.ctx)
             self.ctx = None
