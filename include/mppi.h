@@ -458,8 +458,9 @@ mppi_status mppi_get_controls(mppi_ctx* ctx, float* d_U);
 
 /* ---- ordering with the caller's streams -----------------------------------
  * For callers whose tensors live on other streams than the context's (one event
- * each way, kept by the context; nothing waits on the host; a stream of the
- * context's device):
+ * each way, kept by the context; nothing waits on the host).  hip_stream is a
+ * stream of the context's device, which need not be the current one; NULL is that
+ * device's null stream:
  *   mppi_wait_stream    what the context is given from now on starts after
  *                       everything hip_stream holds now;
  *   mppi_release_stream what hip_stream is given from now on starts after

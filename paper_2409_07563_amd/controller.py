@@ -184,8 +184,8 @@ class Controller:
         self.ctx = ctx
         self._lib = L
         self._joined = False  # a call of this controller is part of a captured graph
-        # where a tensor has to live to be handed to the library as it is
-        self._dev_exact = torch.empty(0, device=self.device).device
+        # the device the controller lives on, whichever is current later
+        self._home = torch.empty(0, device=self.device).device
         self._off = {k: self._offsets(k) for k in (_abi.PACKED_STATE, _abi.PACKED_CONTROLS,
                                                    _abi.PACKED_SAMPLES, _abi.PACKED_NOISE)}
         self.set_state(np.concatenate([np.asarray(q.x0, np.float32).ravel() for q in probs]))
@@ -193,18 +193,22 @@ class Controller:
 
     # -- streams ------------------------------------------------------------
     def _current(self) -> int:
-        """Handle of torch's current stream on the controller's device."""
-        i = self.device.index
-        return _raw_stream(torch.cuda.current_device() if i is None else i)
+        """Handle of torch's current stream on the controller's device (0 is the
+        default stream of every device; the library knows which one is meant)."""
+        return _raw_stream(self._home.index)
 
     def _capturing(self) -> bool:
-        return torch.cuda.is_current_stream_capturing()
+        """Whether torch's current stream on the controller's device is under capture."""
+        if torch.cuda.current_device() == self._home.index:
+            return torch.cuda.is_current_stream_capturing()
+        with torch.cuda.device(self._home):
+            return torch.cuda.is_current_stream_capturing()
 
     def _enter(self) -> None:
         """Order the library's stream after torch's current stream."""
         if self._capturing():
             self._joined = True
-            self.stream.wait_stream(torch.cuda.current_stream(self.device))
+            self.stream.wait_stream(torch.cuda.current_stream(self._home))
         else:
             check(self._lib.mppi_wait_stream(self.ctx, self._current()))
 
@@ -224,22 +228,22 @@ class Controller:
         """Order torch's current stream after the library's work on t, which was
         allocated on that stream before the last _enter()."""
         if self._capturing():
-            torch.cuda.current_stream(self.device).wait_stream(self.stream)
+            torch.cuda.current_stream(self._home).wait_stream(self.stream)
         else:
             check(self._lib.mppi_release_stream(self.ctx, self._current()))
         return t
 
     def _empty(self, shape, dtype=torch.float32) -> torch.Tensor:
-        return torch.empty(shape, dtype=dtype, device=self.device)
+        return torch.empty(shape, dtype=dtype, device=self._home)
 
     def _dev(self, a, n: int) -> torch.Tensor:
         self._enter()
         if (torch.is_tensor(a) and a.dtype == torch.float32 and a.is_contiguous()
-                and a.numel() == n and a.device == self._dev_exact):
+                and a.numel() == n and a.device == self._home):
             return a.detach()
         t = torch.as_tensor(np.asarray(a, np.float32) if not torch.is_tensor(a) else a)
         with torch.cuda.stream(self.stream):
-            t = t.to(device=self.device, dtype=torch.float32).contiguous().reshape(n)
+            t = t.to(device=self._home, dtype=torch.float32).contiguous().reshape(n)
         return t
 
     # -- packing ------------------------------------------------------------

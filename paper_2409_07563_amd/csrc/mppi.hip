@@ -652,8 +652,9 @@ struct mppi_ctx {
   mppi_tuning tune{};                     // launch shapes (lanes: instance 0's choice)
   bool tuned = false;                     // mppi_set_tuning or mppi_autotune chose them
   // ordering with the caller's streams (mppi_wait_stream, mppi_release_stream):
-  // events made on first use
+  // events made on first use, on the context's device
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  int device = -1;
   ~mppi_ctx() {
     drop_graphs();
     if (ev_in) (void)hipEventDestroy(ev_in);
@@ -675,11 +676,44 @@ hipError_t tape_reset(mppi_ctx* c) {
   return launch_tape_reset(c->one().at<int32_t>(c->one().L.tape_count), c->stream);
 }
 
-// `after` waits (on the GPU) for what `before` holds now.
-hipError_t order_streams(hipEvent_t* ev, hipStream_t before, hipStream_t after) {
+// The context's device: its stream's, or for the null stream the current one.
+int device_of(hipStream_t stream) {
+  int dev = -1;
+  if (stream && hipStreamGetDevice(stream, &dev) == hipSuccess) return dev;
+  if (stream) (void)hipGetLastError();  // a handle that names no stream object
+  return hipGetDevice(&dev) == hipSuccess ? dev : -1;
+}
+
+// Makes a device current for a scope.  An event belongs to the device it is made
+// on, and the null stream is the current device's.
+class OnDevice {
+ public:
+  explicit OnDevice(int dev) {
+    int cur = -1;
+    status = hipGetDevice(&cur);
+    if (status != hipSuccess || dev < 0 || cur == dev) return;
+    status = hipSetDevice(dev);
+    if (status == hipSuccess) back_ = cur;
+  }
+  ~OnDevice() {
+    if (back_ >= 0) (void)hipSetDevice(back_);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+  hipError_t status;
+
+ private:
+  int back_ = -1;
+};
+
+// `after` waits (on the GPU) for what `before` holds now; both are streams of
+// the context's device.
+hipError_t order_streams(const mppi_ctx* c, hipEvent_t* ev, hipStream_t before,
+                         hipStream_t after) {
   if (before == after) return hipSuccess;
-  hipError_t e = hipSuccess;
-  if (!*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
+  const OnDevice on(c->device);
+  hipError_t e = on.status;
+  if (e == hipSuccess && !*ev) e = hipEventCreateWithFlags(ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventRecord(*ev, before);
   return e == hipSuccess ? hipStreamWaitEvent(after, *ev, 0) : e;
 }
@@ -951,6 +985,7 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
   c->batch = batch;
   c->ws = static_cast<char*>(d_workspace);
   c->stream = static_cast<hipStream_t>(hip_stream);
+  c->device = device_of(c->stream);
   c->C = C;
   c->inst.resize(n_inst);
   std::vector<std::vector<float4>> keep;
@@ -1935,13 +1970,13 @@ mppi_status mppi_get_controls(mppi_ctx* c, float* d_U) {
 
 mppi_status mppi_wait_stream(mppi_ctx* c, void* hip_stream) {
   if (!c) return fail(MPPI_EINVAL, "ctx must not be NULL");
-  HIP_TRY(order_streams(&c->ev_in, static_cast<hipStream_t>(hip_stream), c->stream));
+  HIP_TRY(order_streams(c, &c->ev_in, static_cast<hipStream_t>(hip_stream), c->stream));
   return MPPI_OK;
 }
 
 mppi_status mppi_release_stream(mppi_ctx* c, void* hip_stream) {
   if (!c) return fail(MPPI_EINVAL, "ctx must not be NULL");
-  HIP_TRY(order_streams(&c->ev_out, c->stream, static_cast<hipStream_t>(hip_stream)));
+  HIP_TRY(order_streams(c, &c->ev_out, c->stream, static_cast<hipStream_t>(hip_stream)));
   return MPPI_OK;
 }
 

@@ -76,7 +76,7 @@ def world(monkeypatch):
     c.device = torch.device("cpu")
     c.stream, c.ctx, c._lib = w.lib, 1, Library(w)
     c.batch, c.requires_grad, c.n_inst, c.T, c.m, c.K = False, True, 1, 4, 2, 8
-    c._joined, c._dev_exact = False, torch.device("cpu")
+    c._joined, c._home = False, torch.device("cpu", 0)
     c._off = {k: np.array([0, n]) for k, n in ((_abi.PACKED_STATE, 4), (_abi.PACKED_CONTROLS, 8),
                                                (_abi.PACKED_SAMPLES, 8), (_abi.PACKED_NOISE, 64))}
     w.ctl = c
@@ -121,3 +121,40 @@ def test_close_waits_for_replays(world):
     replay = world.cur.run()
     c.close()
     assert before(replay, c._lib.last("mppi_destroy"))
+
+
+def test_a_controller_of_another_device(world, monkeypatch):
+    """The controller's device is 1 while device 0 is current: the stream it is
+    ordered with and the capture it joins are device 1's."""
+    c = world.ctl
+    c.device, c._home = torch.device("cuda"), torch.device("cuda", 1)
+    other, asked = Stream(33), []
+    world.by_handle[33] = other
+    now = [0]
+
+    @contextlib.contextmanager
+    def device(d):
+        old, now[0] = now[0], d.index
+        yield
+        now[0] = old
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: now[0])
+    monkeypatch.setattr(torch.cuda, "device", device)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing",
+                        lambda: asked.append(now[0]) or (world.capturing and now[0] == 1))
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda d=None: other if (now[0] if d is None else d.index) == 1 else world.cur)
+    monkeypatch.setattr(controller, "_raw_stream", lambda d: {0: 22, 1: 33}[d])
+    monkeypatch.setattr(torch, "empty", lambda shape, dtype=None, device=None:
+                        types.SimpleNamespace(device=device, data_ptr=lambda: 0, reshape=lambda *a: 0,
+                                              view=lambda *a: 0))
+    first = other.run()
+    c.controls()
+    read = c._lib.last("mppi_get_controls")
+    assert before(first, read) and before(read, other.run())
+    assert not before(read, world.cur.run())
+    world.capturing = True
+    second = other.run()
+    c.iterate(1)
+    assert before(second, c._lib.last("mppi_iterate"))
+    assert set(asked) == {1}
