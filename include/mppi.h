@@ -468,6 +468,13 @@ mppi_status mppi_get_controls(mppi_ctx* ctx, float* d_U);
  * Errors: EINVAL (NULL ctx), EDEVICE. */
 mppi_status mppi_wait_stream(mppi_ctx* ctx, void* hip_stream);
 mppi_status mppi_release_stream(mppi_ctx* ctx, void* hip_stream);
+/* mppi_set_state, mppi_set_controls or mppi_set_costs (what: MPPI_PACKED_STATE,
+ * MPPI_PACKED_CONTROLS or MPPI_PACKED_SAMPLES), the array read on hip_stream: it
+ * starts after what hip_stream and the context hold now, what the context is given
+ * from now on starts after it, and what hip_stream is given from now on may write
+ * or free d_src.  Neither stream under capture.  Errors: EINVAL (NULL, unknown
+ * array), EDEVICE. */
+mppi_status mppi_put(mppi_ctx* ctx, int32_t what, const float* d_src, void* hip_stream);
 
 enum {
   MPPI_DEBUG_NOISE = 0,   /* float eps[T][m][K] of the last sampling */

@@ -94,6 +94,7 @@ EXPORTS = {
     "mppi_get_controls": (C.c_int, [C.c_void_p, C.c_void_p]),
     "mppi_wait_stream": (C.c_int, [C.c_void_p, C.c_void_p]),
     "mppi_release_stream": (C.c_int, [C.c_void_p, C.c_void_p]),
+    "mppi_put": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]),
     "mppi_get_debug": (C.c_int, [C.c_void_p, C.c_int32, C.c_void_p]),
     "mppi_backward": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p]),
     "mppi_backward_iters": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),

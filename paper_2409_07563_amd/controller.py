@@ -3,10 +3,11 @@
 PyTorch supplies the device memory (the workspace and the x0 / u / U buffers)
 and a HIP stream; the arithmetic of every step of the iteration runs in
 libmppi.so's kernels.  The controller works on a stream of its own (default
-priority) so that `iterate` can replay a captured hipGraph.  A call that reads a
-caller's tensor first orders that stream after torch's current stream, and
-every tensor a call returns is ordered back onto torch's current stream, so
-callers can ignore streams; the other calls (shift, sample, rollout, update,
+priority) so that `iterate` can replay a captured hipGraph.  A caller's tensor is
+read on torch's current stream, so it may be written or freed right after the
+call, and the library's stream is ordered after that; every tensor a call returns
+is ordered back onto torch's current stream.  Callers can ignore streams.  The
+other calls (shift, sample, rollout, update,
 iterate, set_iteration) touch only the context's own memory and follow each other
 on its stream.  While torch's current stream is under capture they are ordered
 after it too, which makes them part of the capture; a replay then runs them on
@@ -14,7 +15,7 @@ the stream it is launched on, so from the first such call on every call of that
 controller is ordered after torch's current stream, and that stream after it.
 
 The ordering uses the library's two events (mppi_wait_stream,
-mppi_release_stream): a torch Stream.wait_stream makes a new event and costs 19 us
+mppi_release_stream, mppi_put): a torch Stream.wait_stream makes a new event and costs 19 us
 of host time, and a control call made four of them.  Returned tensors belong to
 torch's current stream: they are allocated there before the library's stream is
 ordered after it, and that stream is ordered after the library's work on them, so
@@ -184,6 +185,7 @@ class Controller:
         self.ctx = ctx
         self._lib = L
         self._joined = False  # a call of this controller is part of a captured graph
+        self._captured: dict = {}
         # the device the controller lives on, whichever is current later
         self._home = torch.empty(0, device=self.device).device
         self._off = {k: self._offsets(k) for k in (_abi.PACKED_STATE, _abi.PACKED_CONTROLS,
@@ -224,9 +226,9 @@ class Controller:
         if self._joined and not self._capturing():
             check(self._lib.mppi_release_stream(self.ctx, self._current()))
 
-    def _leave(self, t: torch.Tensor) -> torch.Tensor:
-        """Order torch's current stream after the library's work on t, which was
-        allocated on that stream before the last _enter()."""
+    def _leave(self, t=None):
+        """Order torch's current stream after the library's work (on t, which was
+        allocated on that stream before the last _enter())."""
         if self._capturing():
             torch.cuda.current_stream(self._home).wait_stream(self.stream)
         else:
@@ -236,15 +238,37 @@ class Controller:
     def _empty(self, shape, dtype=torch.float32) -> torch.Tensor:
         return torch.empty(shape, dtype=dtype, device=self._home)
 
-    def _dev(self, a, n: int) -> torch.Tensor:
-        self._enter()
-        if (torch.is_tensor(a) and a.dtype == torch.float32 and a.is_contiguous()
-                and a.numel() == n and a.device == self._home):
-            return a.detach()
+    def _f32(self, a, n: int) -> torch.Tensor:
+        """a as n packed floats on the controller's device."""
         t = torch.as_tensor(np.asarray(a, np.float32) if not torch.is_tensor(a) else a)
+        return t.to(device=self._home, dtype=torch.float32).contiguous().reshape(n)
+
+    def _as_is(self, a, n: int) -> bool:
+        """Whether a is what _f32 would give."""
+        return (torch.is_tensor(a) and a.dtype == torch.float32 and a.is_contiguous()
+                and a.numel() == n and a.device == self._home)
+
+    def _dev(self, a, n: int) -> torch.Tensor:
+        """a for the library's stream, which is ordered after torch's current one."""
+        self._enter()
+        if self._as_is(a, n):
+            return a.detach()
         with torch.cuda.stream(self.stream):
-            t = t.to(device=self._home, dtype=torch.float32).contiguous().reshape(n)
-        return t
+            return self._f32(a, n)
+
+    def _put(self, what: int, captured, a) -> None:
+        """Hand the caller's a over, under capture by a call of the library's stream
+        (which the capture joins)."""
+        n = int(self._off[what][-1])
+        if self._capturing():
+            t = self._dev(a, n)
+            check(captured(self.ctx, t.data_ptr()))
+            self._leave()
+            self._captured[what] = t  # replays read it again
+        else:
+            t = a if self._as_is(a, n) else self._f32(a, n)
+            check(self._lib.mppi_put(self.ctx, what, t.data_ptr(), self._current()))
+            self._done()
 
     # -- packing ------------------------------------------------------------
     def _offsets(self, kind: int) -> np.ndarray:
@@ -262,14 +286,10 @@ class Controller:
 
     # -- state --------------------------------------------------------------
     def set_state(self, x0) -> None:
-        t = self._dev(x0, int(self._off[_abi.PACKED_STATE][-1]))
-        check(self._lib.mppi_set_state(self.ctx, t.data_ptr()))
-        self._x0 = t  # alive until the enqueued copy has run (stream order)
+        self._put(_abi.PACKED_STATE, self._lib.mppi_set_state, x0)
 
     def set_controls(self, u) -> None:
-        t = self._dev(u, int(self._off[_abi.PACKED_CONTROLS][-1]))
-        check(self._lib.mppi_set_controls(self.ctx, t.data_ptr()))
-        self._u = t
+        self._put(_abi.PACKED_CONTROLS, self._lib.mppi_set_controls, u)
 
     def set_iteration(self, iteration: int) -> None:
         self._own()
@@ -296,9 +316,7 @@ class Controller:
         self._done()
 
     def set_costs(self, S) -> None:
-        t = self._dev(S, int(self._off[_abi.PACKED_SAMPLES][-1]))
-        check(self._lib.mppi_set_costs(self.ctx, t.data_ptr()))
-        self._S = t
+        self._put(_abi.PACKED_SAMPLES, self._lib.mppi_set_costs, S)
 
     def update(self) -> None:
         self._own()

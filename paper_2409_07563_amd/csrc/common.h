@@ -317,6 +317,7 @@ hipError_t launch_weights_only(const float* d_S, int K, float lambda, float* d_e
                                DevState* d_scratch_state, hipStream_t stream);
 // The differentiation tape: start over (count = 0).
 hipError_t launch_tape_reset(int32_t* d_count, hipStream_t stream);
+hipError_t launch_copy(const float* d_src, float* d_dst, int64_t n, hipStream_t stream);
 // u[t] <- u[min(t + steps, T - 1)] (fill 0) or 0 past the horizon (fill 1)
 hipError_t launch_shift(float* d_u, int T, int m, int steps, int fill, hipStream_t stream);
 hipError_t launch_batch_shift(const BatchPlan& b, int steps, int fill, hipStream_t stream);

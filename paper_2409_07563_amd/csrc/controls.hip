@@ -78,4 +78,20 @@ hipError_t launch_tape_reset(int32_t* d_count, hipStream_t stream) {
   return hipGetLastError();
 }
 
+__global__ __launch_bounds__(kControlsBlock) void copy_kernel(const float* __restrict__ src,
+                                                              float* __restrict__ dst,
+                                                              int64_t n) {
+  const int64_t step = int64_t{gridDim.x} * kControlsBlock;
+  for (int64_t i = int64_t{blockIdx.x} * kControlsBlock + threadIdx.x; i < n; i += step)
+    dst[i] = src[i];
+}
+
+hipError_t launch_copy(const float* d_src, float* d_dst, int64_t n, hipStream_t stream) {
+  if (n < 1) return hipSuccess;
+  const int64_t blocks = (n + kControlsBlock - 1) / kControlsBlock;
+  hipLaunchKernelGGL(copy_kernel, dim3(static_cast<unsigned>(blocks < 4096 ? blocks : 4096)),
+                     dim3(kControlsBlock), 0, stream, d_src, d_dst, n);
+  return hipGetLastError();
+}
+
 }  // namespace mppi

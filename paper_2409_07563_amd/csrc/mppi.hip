@@ -655,6 +655,14 @@ struct mppi_ctx {
   // events made on first use, on the context's device
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   int device = -1;
+  // the device's null stream has been ordered after everything the context was
+  // given so far (other streams may end and leave their handle to a new one)
+  bool null_after = false;
+  // the stream, to give the context work
+  hipStream_t work() {
+    null_after = false;
+    return stream;
+  }
   ~mppi_ctx() {
     drop_graphs();
     if (ev_in) (void)hipEventDestroy(ev_in);
@@ -673,7 +681,7 @@ namespace {
 hipError_t tape_reset(mppi_ctx* c) {
   if (c->batch || !c->one().grad) return hipSuccess;
   c->tape_external = false;
-  return launch_tape_reset(c->one().at<int32_t>(c->one().L.tape_count), c->stream);
+  return launch_tape_reset(c->one().at<int32_t>(c->one().L.tape_count), c->work());
 }
 
 // The context's device: its stream's, or for the null stream the current one.
@@ -933,8 +941,8 @@ mppi_status upload_sample_tiles(mppi_ctx* c, int tile) {
                                           c->C.n_sample_tiles, tile, K.data(), n_inst);
   if (!bad.empty()) return fail(MPPI_EINVAL, "sample work list: %s", bad.c_str());
   hipError_t e = hipMemcpyAsync(c->ws + c->C.sample_tiles, tiles.data(),
-                                sizeof(WorkItem) * tiles.size(), hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                                sizeof(WorkItem) * tiles.size(), hipMemcpyHostToDevice, c->work());
+  if (e == hipSuccess) e = hipStreamSynchronize(c->work());
   if (e != hipSuccess) return hip_fail(e, "sample work list upload");
   c->plan.n_sample_tiles = static_cast<int>(tiles.size());
   c->plan.tile = tile;
@@ -995,8 +1003,8 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
   for (int i = 0; i < n_inst; ++i) {
     Instance& I = c->inst[i];
     mppi_status s =
-        setup_instance(&cfgs[i], &params[i], batch, c->ws + C.slice[i], c->stream, &I, &keep);
-    if (s != MPPI_OK) { (void)hipStreamSynchronize(c->stream); delete c; return s; }
+        setup_instance(&cfgs[i], &params[i], batch, c->ws + C.slice[i], c->work(), &I, &keep);
+    if (s != MPPI_OK) { (void)hipStreamSynchronize(c->work()); delete c; return s; }
     I.st = reinterpret_cast<DevState*>(c->ws + C.states) + i;
     I.x0 = reinterpret_cast<float*>(c->ws + C.x0) + ox;
     I.u = reinterpret_cast<float*>(c->ws + C.u) + ou;
@@ -1010,10 +1018,10 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
   }
   c->n_x0 = ox; c->n_u = ou; c->n_S = oS;
   hipError_t e = hipMemcpyAsync(c->ws + C.states, states.data(), sizeof(DevState) * n_inst,
-                                hipMemcpyHostToDevice, c->stream);
+                                hipMemcpyHostToDevice, c->work());
   std::vector<float> zeros(ou, 0.0f);
   if (e == hipSuccess)
-    e = hipMemcpyAsync(c->ws + C.u, zeros.data(), sizeof(float) * ou, hipMemcpyHostToDevice, c->stream);
+    e = hipMemcpyAsync(c->ws + C.u, zeros.data(), sizeof(float) * ou, hipMemcpyHostToDevice, c->work());
 
   // batch tables
   std::vector<BatchInst> bi;
@@ -1072,15 +1080,15 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
                                             static_cast<int64_t>(row_tiles.size()),
                                             C.n_row_tiles, rpb, TM.data(), n_inst);
     if (!bad.empty()) {
-      (void)hipStreamSynchronize(c->stream);
+      (void)hipStreamSynchronize(c->work());
       delete c;
       return fail(MPPI_EINVAL, "row work list: %s", bad.c_str());
     }
     e = hipMemcpyAsync(c->ws + C.insts, bi.data(), sizeof(BatchInst) * n_inst,
-                       hipMemcpyHostToDevice, c->stream);
+                       hipMemcpyHostToDevice, c->work());
     if (e == hipSuccess)
       e = hipMemcpyAsync(c->ws + C.row_tiles, row_tiles.data(),
-                         sizeof(WorkItem) * row_tiles.size(), hipMemcpyHostToDevice, c->stream);
+                         sizeof(WorkItem) * row_tiles.size(), hipMemcpyHostToDevice, c->work());
     BatchPlan& P = c->plan;
     P.insts = reinterpret_cast<const BatchInst*>(c->ws + C.insts);
     P.sample_tiles = reinterpret_cast<const int2*>(c->ws + C.sample_tiles);
@@ -1097,7 +1105,7 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
     P.fused_items = reinterpret_cast<const int2*>(c->ws + C.one_items);
     P.n_fused_items = 0;
     P.done = reinterpret_cast<uint32_t*>(c->ws + C.done);
-    if (e == hipSuccess) e = hipMemsetAsync(P.done, 0, sizeof(uint32_t) * n_inst, c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(P.done, 0, sizeof(uint32_t) * n_inst, c->work());
     if (one_ok && batch_one_launch_supported(cfgs[0].dynamics, cfgs[0].integrator, cfgs[0].cost) &&
         e == hipSuccess) {
       std::vector<int32_t> Kv(n_inst), Tv(n_inst);
@@ -1107,19 +1115,19 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
                                                static_cast<int64_t>(one_items.size()),
                                                C.n_one_items, kBatchMaxTile, Kv.data(), n_inst);
       if (!bad2.empty()) {
-        (void)hipStreamSynchronize(c->stream);
+        (void)hipStreamSynchronize(c->work());
         delete c;
         return fail(MPPI_EINVAL, "one-launch work list: %s", bad2.c_str());
       }
       e = hipMemcpyAsync(c->ws + C.one_items, one_items.data(),
-                         sizeof(WorkItem) * one_items.size(), hipMemcpyHostToDevice, c->stream);
+                         sizeof(WorkItem) * one_items.size(), hipMemcpyHostToDevice, c->work());
       P.n_fused_items = static_cast<int>(one_items.size());
     }
   }
   // a single context's one-launch form: its zeroed tile counter
   if (C.one_single && e == hipSuccess)
-    e = hipMemsetAsync(c->ws + C.done, 0, sizeof(uint32_t), c->stream);
-  const hipError_t e2 = hipStreamSynchronize(c->stream);  // host staging buffers die here
+    e = hipMemsetAsync(c->ws + C.done, 0, sizeof(uint32_t), c->work());
+  const hipError_t e2 = hipStreamSynchronize(c->work());  // host staging buffers die here
   if (e == hipSuccess) e = e2;
   // default launch shapes: four lanes per sample where one lane per sample
   // would leave most SIMDs idle
@@ -1151,10 +1159,10 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
 
 // ---- the phases of one iteration on a context -------------------------------
 hipError_t phase_sample(mppi_ctx* c) {
-  if (c->batch) return launch_batch_noise(c->plan, c->stream);
+  if (c->batch) return launch_batch_noise(c->plan, c->work());
   const Instance& I = c->one();
   return launch_noise(I.cfg.seed, &I.st->iteration, 0u, I.cfg.instance, I.K, I.T, I.m,
-                      I.cfg.sigma, I.eps(), I.L.ldk, c->stream, c->tune.noise_calls, I.dp.sigma_t,
+                      I.cfg.sigma, I.eps(), I.L.ldk, c->work(), c->tune.noise_calls, I.dp.sigma_t,
                       I.dp.mean_sample != 0, I.word(I.cur));
 }
 
@@ -1231,23 +1239,23 @@ hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
   const bool accurate = (I.cfg.flags & MPPI_F_ACCURATE_TRIG) != 0;
   if (c->batch)
     return launch_batch_rollout(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, count,
-                                c->plan, c->stream);
+                                c->plan, c->work());
   if (I.hidden || I.grad) {
     float* ckpt = I.grad ? I.at<float>(I.L.ckpt) : nullptr;
     if (I.grad) {
       hipError_t e = hipMemcpyAsync(I.at<float>(I.L.u_roll), I.u, sizeof(float) * I.TM,
-                                    hipMemcpyDeviceToDevice, c->stream);
+                                    hipMemcpyDeviceToDevice, c->work());
       if (e != hipSuccess) return e;
     }
     return launch_rollout_tiles(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.dp, I.x0,
                                 I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, ckpt, I.ckpt_every,
-                                c->stream, c->tune.rollout_block / kWave);
+                                c->work(), c->tune.rollout_block / kWave);
   }
   if (c->tune.rollout_form == MPPI_ROLLOUT_SPLIT)
     return launch_rollout_split(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.lanes,
                                 I.dp, I.x0, I.u, I.eps(), I.L.ldk, I.K, I.T, I.at<float>(I.L.traj),
                                 I.at<float>(I.L.split_part), I.S, count ? I.crashes : nullptr,
-                                c->stream,
+                                c->work(),
                                 c->tune.rollout_block, c->tune.cost_waves);
   NoiseJob job{};
   if (next) job = next_noise_job(c);
@@ -1257,18 +1265,18 @@ hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
   if (scan)
     return launch_rollout_scan(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.dp, I.x0,
                                I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
-                               c->stream, c->tuned ? c->tune.rollout_block : 256,
+                               c->work(), c->tuned ? c->tune.rollout_block : 256,
                                next ? &job : nullptr, scan);
   return launch_rollout(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.lanes, I.dp, I.x0,
                         I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
-                        c->stream, c->tuned ? c->tune.rollout_block : default_rollout_block(c),
+                        c->work(), c->tuned ? c->tune.rollout_block : default_rollout_block(c),
                         next ? &job : nullptr);
 }
 
 // next: the weights launch also draws the next iteration's noise into the
 // other buffer (the caller then switches buffers).
 hipError_t phase_update(mppi_ctx* c, bool next = false) {
-  if (c->batch) return launch_batch_update(c->plan, c->stream);
+  if (c->batch) return launch_batch_update(c->plan, c->work());
   const Instance& I = c->one();
   TapeRef tape;
   if (I.grad) {
@@ -1283,14 +1291,14 @@ hipError_t phase_update(mppi_ctx* c, bool next = false) {
   if (next) job = next_noise_job(c);
   if (c->tune.update_form == MPPI_UPDATE_ONE_PASS)
     return launch_update_one_pass(I.S, I.eps(), I.L.ldk, I.K, I.TM, I.cfg.lambda,
-                                  step_size(I.cfg), I.u, I.st, c->stream, I.dp.n_plain,
+                                  step_size(I.cfg), I.u, I.st, c->work(), I.dp.n_plain,
                                   next ? &job : nullptr);
   if (c->tune.update_form == MPPI_UPDATE_CHUNKED)
     return launch_update_chunked(I.S, I.eps(), I.L.ldk, I.K, I.TM, I.cfg.lambda,
                                  step_size(I.cfg), I.e(), I.at<float4>(I.L.wpart), I.u, I.st,
-                                 c->stream, I.dp.n_plain, next ? &job : nullptr);
+                                 c->work(), I.dp.n_plain, next ? &job : nullptr);
   return launch_softmin_update(I.S, I.eps(), I.L.ldk, I.K, I.TM, I.cfg.lambda, step_size(I.cfg),
-                               I.e(), I.u, I.st, c->stream, I.dp.n_plain, tape,
+                               I.e(), I.u, I.st, c->work(), I.dp.n_plain, tape,
                                next ? &job : nullptr);
 }
 
@@ -1330,13 +1338,13 @@ hipError_t phase_iteration(mppi_ctx* c, int i, bool ahead) {
   hipError_t e = hipSuccess;
   if (one_launch_single(c))
     return launch_di_iteration(single_inst(c), reinterpret_cast<uint32_t*>(c->ws + c->C.done),
-                               c->stream);
+                               c->work());
   if (c->batch && c->tune.batch_form == MPPI_BATCH_ONE_LAUNCH) {
     const Instance& I = c->one();
     const bool count = (I.cfg.flags & MPPI_F_DEBUG) && uses_circles(I.cfg.cost);
     const bool accurate = (I.cfg.flags & MPPI_F_ACCURATE_TRIG) != 0;
     return launch_batch_one_launch(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, count,
-                                   c->plan, c->stream);
+                                   c->plan, c->work());
   }
   if (c->batch || !c->one().ahead_ok) {
     e = phase_sample(c);
@@ -1595,9 +1603,9 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
   // seconds per launch of fn, after one warm-up launch
   auto time_it = [&](auto fn, double* us) -> hipError_t {
     hipError_t err = fn();
-    if (err == hipSuccess) err = hipEventRecord(a, c->stream);
+    if (err == hipSuccess) err = hipEventRecord(a, c->work());
     for (int r = 0; r < reps && err == hipSuccess; ++r) err = fn();
-    if (err == hipSuccess) err = hipEventRecord(b, c->stream);
+    if (err == hipSuccess) err = hipEventRecord(b, c->work());
     if (err == hipSuccess) err = hipEventSynchronize(b);
     float ms = 0.0f;
     if (err == hipSuccess) err = hipEventElapsedTime(&ms, a, b);
@@ -1667,11 +1675,11 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
       std::vector<float> u_save(static_cast<size_t>(c->n_u));
       std::vector<DevState> st_save(c->inst.size());
       e = hipMemcpyAsync(u_save.data(), c->ws + c->C.u, sizeof(float) * u_save.size(),
-                         hipMemcpyDeviceToHost, c->stream);
+                         hipMemcpyDeviceToHost, c->work());
       if (e == hipSuccess)
         e = hipMemcpyAsync(st_save.data(), c->ws + c->C.states, sizeof(DevState) * st_save.size(),
-                           hipMemcpyDeviceToHost, c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                           hipMemcpyDeviceToHost, c->work());
+      if (e == hipSuccess) e = hipStreamSynchronize(c->work());
       if (e != hipSuccess) return done(hip_fail(e, "autotune save"));
       std::vector<mppi_tuning> forms;
       mppi_tuning a = best;
@@ -1688,11 +1696,11 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
         return mppi_iterate(c, 1) == MPPI_OK ? hipSuccess : hipErrorLaunchFailure;
       }, &best, 0.05);
       e = hipMemcpyAsync(c->ws + c->C.u, u_save.data(), sizeof(float) * u_save.size(),
-                         hipMemcpyHostToDevice, c->stream);
+                         hipMemcpyHostToDevice, c->work());
       if (e == hipSuccess)
         e = hipMemcpyAsync(c->ws + c->C.states, st_save.data(), sizeof(DevState) * st_save.size(),
-                           hipMemcpyHostToDevice, c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                           hipMemcpyHostToDevice, c->work());
+      if (e == hipSuccess) e = hipStreamSynchronize(c->work());
       if (st != MPPI_OK) return done(st);
       if (e != hipSuccess) return done(hip_fail(e, "autotune restore"));
     }
@@ -1775,11 +1783,11 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
       DevState st_save{};
       const int cur_save = c->inst[0].cur;
       e = hipMemcpyAsync(u_save.data(), c->ws + c->C.u, sizeof(float) * u_save.size(),
-                         hipMemcpyDeviceToHost, c->stream);
+                         hipMemcpyDeviceToHost, c->work());
       if (e == hipSuccess)
         e = hipMemcpyAsync(&st_save, c->ws + c->C.states, sizeof(DevState), hipMemcpyDeviceToHost,
-                           c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                           c->work());
+      if (e == hipSuccess) e = hipStreamSynchronize(c->work());
       if (e != hipSuccess) return done(hip_fail(e, "autotune save"));
       std::vector<mppi_tuning> forms;
       mppi_tuning a = best;
@@ -1796,11 +1804,11 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
       c->inst[0].cur = cur_save;
       c->ahead = false;
       e = hipMemcpyAsync(c->ws + c->C.u, u_save.data(), sizeof(float) * u_save.size(),
-                         hipMemcpyHostToDevice, c->stream);
+                         hipMemcpyHostToDevice, c->work());
       if (e == hipSuccess)
         e = hipMemcpyAsync(c->ws + c->C.states, &st_save, sizeof(DevState), hipMemcpyHostToDevice,
-                           c->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+                           c->work());
+      if (e == hipSuccess) e = hipStreamSynchronize(c->work());
       if (st != MPPI_OK) return done(st);
       if (e != hipSuccess) return done(hip_fail(e, "autotune restore"));
     }
@@ -1810,7 +1818,7 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
   // the noise and cost buffers now hold this iteration's sampling and rollout
   e = phase_sample(c);
   if (e == hipSuccess) e = phase_rollout(c);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(c->work());
   if (e != hipSuccess) return done(hip_fail(e, "autotune launch"));
   c->have_noise = c->have_costs = c->rollout_fresh = true;
   c->grad_ready = false;
@@ -1821,7 +1829,7 @@ mppi_status mppi_autotune(mppi_ctx* c, int32_t reps, char* report, size_t report
 mppi_status mppi_set_state(mppi_ctx* c, const float* d_x0) {
   if (!c || !d_x0) return fail(MPPI_EINVAL, "ctx and d_x0 must not be NULL");
   HIP_TRY(hipMemcpyAsync(c->ws + c->C.x0, d_x0, sizeof(float) * c->n_x0, hipMemcpyDeviceToDevice,
-                         c->stream));
+                         c->work()));
   HIP_TRY(tape_reset(c));
   c->have_state = true;
   return MPPI_OK;
@@ -1830,7 +1838,7 @@ mppi_status mppi_set_state(mppi_ctx* c, const float* d_x0) {
 mppi_status mppi_set_controls(mppi_ctx* c, const float* d_u) {
   if (!c || !d_u) return fail(MPPI_EINVAL, "ctx and d_u must not be NULL");
   HIP_TRY(hipMemcpyAsync(c->ws + c->C.u, d_u, sizeof(float) * c->n_u, hipMemcpyDeviceToDevice,
-                         c->stream));
+                         c->work()));
   HIP_TRY(tape_reset(c));
   return MPPI_OK;
 }
@@ -1841,10 +1849,10 @@ mppi_status mppi_shift(mppi_ctx* c, int32_t steps, int32_t fill) {
   if (fill != MPPI_SHIFT_HOLD && fill != MPPI_SHIFT_ZERO)
     return fail(MPPI_EINVAL, "fill must be MPPI_SHIFT_HOLD or MPPI_SHIFT_ZERO");
   if (c->batch) {
-    HIP_TRY(launch_batch_shift(c->plan, steps, fill, c->stream));
+    HIP_TRY(launch_batch_shift(c->plan, steps, fill, c->work()));
   } else {
     const Instance& I = c->one();
-    HIP_TRY(launch_shift(I.u, I.T, I.m, steps, fill, c->stream));
+    HIP_TRY(launch_shift(I.u, I.T, I.m, steps, fill, c->work()));
   }
   HIP_TRY(tape_reset(c));
   return MPPI_OK;
@@ -1854,9 +1862,9 @@ mppi_status mppi_set_iteration(mppi_ctx* c, uint32_t iteration) {
   if (!c) return fail(MPPI_EINVAL, "ctx must not be NULL");
   c->ahead = false;  // the word or a noise buffer may change
   if (c->batch) {
-    HIP_TRY(launch_batch_set_iteration(c->plan, iteration, c->stream));
+    HIP_TRY(launch_batch_set_iteration(c->plan, iteration, c->work()));
   } else {
-    HIP_TRY(launch_set_iteration(c->one().st, iteration, c->stream));
+    HIP_TRY(launch_set_iteration(c->one().st, iteration, c->work()));
   }
   return MPPI_OK;
 }
@@ -1887,7 +1895,7 @@ mppi_status mppi_set_costs(mppi_ctx* c, const float* d_costs) {
   if (!c || !d_costs) return fail(MPPI_EINVAL, "ctx and d_costs must not be NULL");
   c->ahead = false;  // the word or a noise buffer may change
   HIP_TRY(hipMemcpyAsync(c->ws + c->C.S, d_costs, sizeof(float) * c->n_S, hipMemcpyDeviceToDevice,
-                         c->stream));
+                         c->work()));
   c->have_costs = true;
   c->rollout_fresh = c->grad_ready = false;
   return MPPI_OK;
@@ -1928,7 +1936,7 @@ mppi_status mppi_iterate(mppi_ctx* c, int32_t num_iters) {
   // which reaches the GPU sooner than a graph launch, and the null stream
   // cannot be captured
   if (single) c->inst[0].cur = start;
-  if (c->stream == nullptr || num_iters == 1) {
+  if (c->work() == nullptr || num_iters == 1) {
     for (int i = 0; i < num_iters; ++i) {
       hipError_t e = phase_iteration(c, i, ahead);
       if (e != hipSuccess) {
@@ -1942,10 +1950,10 @@ mppi_status mppi_iterate(mppi_ctx* c, int32_t num_iters) {
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
     hipGraph_t g = nullptr;
-    HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
+    HIP_TRY(hipStreamBeginCapture(c->work(), hipStreamCaptureModeRelaxed));
     hipError_t e = hipSuccess;
     for (int i = 0; i < num_iters && e == hipSuccess; ++i) e = phase_iteration(c, i, ahead);
-    const hipError_t ec = hipStreamEndCapture(c->stream, &g);
+    const hipError_t ec = hipStreamEndCapture(c->work(), &g);
     if (single) c->inst[0].cur = last;
     if (e != hipSuccess || ec != hipSuccess) {
       if (g) (void)hipGraphDestroy(g);
@@ -1957,14 +1965,14 @@ mppi_status mppi_iterate(mppi_ctx* c, int32_t num_iters) {
     if (e != hipSuccess) return hip_fail(e, "graph instantiation");
     it = c->graphs.emplace(key, exec).first;
   }
-  HIP_TRY(hipGraphLaunch(it->second, c->stream));
+  HIP_TRY(hipGraphLaunch(it->second, c->work()));
   return finish();
 }
 
 mppi_status mppi_get_controls(mppi_ctx* c, float* d_U) {
   if (!c || !d_U) return fail(MPPI_EINVAL, "ctx and d_U must not be NULL");
   HIP_TRY(hipMemcpyAsync(d_U, c->ws + c->C.u, sizeof(float) * c->n_u, hipMemcpyDeviceToDevice,
-                         c->stream));
+                         c->work()));
   return MPPI_OK;
 }
 
@@ -1977,6 +1985,38 @@ mppi_status mppi_wait_stream(mppi_ctx* c, void* hip_stream) {
 mppi_status mppi_release_stream(mppi_ctx* c, void* hip_stream) {
   if (!c) return fail(MPPI_EINVAL, "ctx must not be NULL");
   HIP_TRY(order_streams(c, &c->ev_out, c->stream, static_cast<hipStream_t>(hip_stream)));
+  c->null_after = !hip_stream;
+  return MPPI_OK;
+}
+
+mppi_status mppi_put(mppi_ctx* c, int32_t what, const float* d_src, void* hip_stream) {
+  if (!c || !d_src) return fail(MPPI_EINVAL, "ctx and d_src must not be NULL");
+  size_t dst;
+  int64_t n;
+  switch (what) {
+    case MPPI_PACKED_STATE: dst = c->C.x0; n = c->n_x0; break;
+    case MPPI_PACKED_CONTROLS: dst = c->C.u; n = c->n_u; break;
+    case MPPI_PACKED_SAMPLES: dst = c->C.S; n = c->n_S; break;
+    default: return fail(MPPI_EINVAL, "unknown packed array %d", what);
+  }
+  const hipStream_t s = static_cast<hipStream_t>(hip_stream);
+  {
+    const OnDevice on(c->device);  // a null stream is this device's
+    HIP_TRY(on.status);
+    if (s || !c->null_after) HIP_TRY(order_streams(c, &c->ev_out, c->stream, s));
+    HIP_TRY(launch_copy(d_src, reinterpret_cast<float*>(c->ws + dst), n, s));
+    HIP_TRY(order_streams(c, &c->ev_in, s, c->stream));
+  }
+  if (what == MPPI_PACKED_SAMPLES) {
+    c->ahead = false;  // the costs of another iteration
+    c->have_costs = true;
+    c->rollout_fresh = c->grad_ready = false;
+  } else {
+    HIP_TRY(tape_reset(c));
+    if (what == MPPI_PACKED_STATE) c->have_state = true;
+  }
+  // the tape's count is no array that a later mppi_put writes
+  c->null_after = !s;
   return MPPI_OK;
 }
 
@@ -1987,31 +2027,31 @@ mppi_status mppi_get_debug(mppi_ctx* c, int32_t what, void* d_dst) {
       char* dst = static_cast<char*>(d_dst);
       for (const Instance& I : c->inst) {
         HIP_TRY(hipMemcpy2DAsync(dst, sizeof(float) * I.K, I.eps(), sizeof(float) * I.L.ldk,
-                                 sizeof(float) * I.K, I.TM, hipMemcpyDeviceToDevice, c->stream));
+                                 sizeof(float) * I.K, I.TM, hipMemcpyDeviceToDevice, c->work()));
         dst += sizeof(float) * static_cast<size_t>(I.TM) * I.K;
       }
       return MPPI_OK;
     }
     case MPPI_DEBUG_COSTS:
       HIP_TRY(hipMemcpyAsync(d_dst, c->ws + c->C.S, sizeof(float) * c->n_S,
-                             hipMemcpyDeviceToDevice, c->stream));
+                             hipMemcpyDeviceToDevice, c->work()));
       return MPPI_OK;
     case MPPI_DEBUG_WEIGHTS:
       for (const Instance& I : c->inst) {
         hipError_t e = launch_weights(I.S, I.K, I.cfg.lambda, I.st,
-                                      static_cast<float*>(d_dst) + I.off_S, c->stream);
+                                      static_cast<float*>(d_dst) + I.off_S, c->work());
         if (e != hipSuccess) return hip_fail(e, "weights launch");
       }
       return MPPI_OK;
     case MPPI_DEBUG_STATS:
       HIP_TRY(hipMemcpyAsync(d_dst, c->ws + c->C.states, sizeof(DevState) * c->inst.size(),
-                             hipMemcpyDeviceToDevice, c->stream));
+                             hipMemcpyDeviceToDevice, c->work()));
       return MPPI_OK;
     case MPPI_DEBUG_CRASHES:
       if (!(c->one().cfg.flags & MPPI_F_DEBUG) || !uses_circles(c->one().cfg.cost))
         return fail(MPPI_ESTATE, "crash counts need MPPI_F_DEBUG and a circles cost");
       HIP_TRY(hipMemcpyAsync(d_dst, c->ws + c->C.crashes, sizeof(int32_t) * c->n_S,
-                             hipMemcpyDeviceToDevice, c->stream));
+                             hipMemcpyDeviceToDevice, c->work()));
       return MPPI_OK;
     default:
       return fail(MPPI_EINVAL, "unknown debug buffer %d", what);
@@ -2043,13 +2083,13 @@ mppi_status mppi_set_theta(mppi_ctx* c, const float* host_theta) {
     std::vector<uint4> bfp;
     build_mlp_packs(host_theta, I.hidden, &fwd, &bwd, bf16_of(&I.cfg) ? &bfp : nullptr);
     HIP_TRY(hipMemcpyAsync(I.at<char>(I.L.mlp), fwd.data(), sizeof(float4) * fwd.size(),
-                           hipMemcpyHostToDevice, c->stream));
+                           hipMemcpyHostToDevice, c->work()));
     HIP_TRY(hipMemcpyAsync(I.at<char>(I.L.mlp_bwd), bwd.data(), sizeof(float4) * bwd.size(),
-                           hipMemcpyHostToDevice, c->stream));
+                           hipMemcpyHostToDevice, c->work()));
     if (!bfp.empty())
       HIP_TRY(hipMemcpyAsync(I.at<char>(I.L.mlp_bf), bfp.data(), sizeof(uint4) * bfp.size(),
-                             hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+                             hipMemcpyHostToDevice, c->work()));
+    HIP_TRY(hipStreamSynchronize(c->work()));
   }
   for (int i = 0; i < I.n; ++i) I.dp.w[i] = host_theta[nmlp + i];
   I.dp.inv_wheelbase = static_cast<float>(1.0 / wheelbase);
@@ -2071,7 +2111,7 @@ mppi_status mppi_backward(mppi_ctx* c, const float* d_dL_dU, float* d_grad) {
                                 I.at<float>(I.L.u_roll), I.eps(), I.L.ldk, I.K, I.T, I.e(),
                                 I.cfg.lambda, step_size(I.cfg), I.at<float>(I.L.ckpt),
                                 I.ckpt_every,
-                                I.at<char>(I.L.adj), I.L.adj_layout, I.n_theta, d_grad, c->stream,
+                                I.at<char>(I.L.adj), I.L.adj_layout, I.n_theta, d_grad, c->work(),
                                 c->tune.rollout_block / kWave, false, nullptr,
                                 c->tune.adjoint_tiles);
   if (e != hipSuccess) return hip_fail(e, "adjoint launch");
@@ -2090,8 +2130,8 @@ mppi_status mppi_backward_iters(mppi_ctx* c, const float* d_dL_dU, float* d_grad
   const Instance& I = c->one();
   int32_t n = 0;
   HIP_TRY(hipMemcpyAsync(&n, I.at<int32_t>(I.L.tape_count), sizeof n, hipMemcpyDeviceToHost,
-                         c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
+                         c->work()));
+  HIP_TRY(hipStreamSynchronize(c->work()));
   if (n < 1) return fail(MPPI_ESTATE, "no update since the tape's start");
   if (n > I.tape_cap)
     return fail(MPPI_ESTATE, "more than tape_len = %d updates since the tape's start",
@@ -2101,7 +2141,7 @@ mppi_status mppi_backward_iters(mppi_ctx* c, const float* d_dL_dU, float* d_grad
   float* G = I.at<float>(I.L.tape_G);
   float* ckpt = I.at<float>(I.L.ckpt);
   DevState* scratch_state = I.at<DevState>(I.L.tape_state);
-  HIP_TRY(hipMemcpyAsync(G, d_dL_dU, sizeof(float) * I.TM, hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(hipMemcpyAsync(G, d_dL_dU, sizeof(float) * I.TM, hipMemcpyDeviceToDevice, c->work()));
   // the last taped iteration is still in the buffers (noise, checkpoints,
   // costs, weights) when its update came right after its rollout and nothing
   // has run since
@@ -2112,26 +2152,26 @@ mppi_status mppi_backward_iters(mppi_ctx* c, const float* d_dL_dU, float* d_grad
     if (!(i == n - 1 && last_in_place)) {
       // rebuild iteration i from its tape entry: noise, checkpointing rollout, weights
       e = launch_noise(I.cfg.seed, I.at<uint32_t>(I.L.tape_word) + i, 0u, I.cfg.instance, I.K,
-                       I.T, I.m, I.cfg.sigma, I.eps(), I.L.ldk, c->stream, c->tune.noise_calls,
+                       I.T, I.m, I.cfg.sigma, I.eps(), I.L.ldk, c->work(), c->tune.noise_calls,
                        I.dp.sigma_t, I.dp.mean_sample != 0);
       if (e == hipSuccess)
         e = launch_rollout_tiles(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.dp,
                                  I.x0, u_i, I.eps(), I.L.ldk, I.K, I.T, I.S, ckpt, I.ckpt_every,
-                                 c->stream, waves);
+                                 c->work(), waves);
       if (e == hipSuccess)
-        e = launch_weights_only(I.S, I.K, I.cfg.lambda, I.e(), scratch_state, c->stream);
+        e = launch_weights_only(I.S, I.K, I.cfg.lambda, I.e(), scratch_state, c->work());
     }
     // then its reverse pass: grad (+)= sum_k a_k dJ_k/dtheta, G += sum_k a_k dJ_k/du_i
     if (e == hipSuccess)
       e = launch_adjoint(I.dp, accurate, I.hidden, G, u_i, I.eps(), I.L.ldk, I.K, I.T, I.e(),
                          I.cfg.lambda, step_size(I.cfg), ckpt, I.ckpt_every, I.at<char>(I.L.adj),
-                         I.L.adj_layout, I.n_theta, d_grad, c->stream, waves, i != n - 1, G,
+                         I.L.adj_layout, I.n_theta, d_grad, c->work(), waves, i != n - 1, G,
                          c->tune.adjoint_tiles);
     if (e != hipSuccess) return hip_fail(e, "reverse pass launch");
   }
   if (d_dL_du0)
     HIP_TRY(hipMemcpyAsync(d_dL_du0, G, sizeof(float) * I.TM, hipMemcpyDeviceToDevice,
-                           c->stream));
+                           c->work()));
   // the noise, cost and weight buffers now hold the first taped iteration's
   c->rollout_fresh = c->grad_ready = false;
   return MPPI_OK;

@@ -50,6 +50,13 @@ class Library:
         self.world.by_handle[handle].wait_stream(self.world.lib)
         return 0
 
+    def mppi_put(self, ctx, what, ptr, handle):
+        cur = self.world.by_handle[handle]
+        cur.wait_stream(self.world.lib)
+        self.ops.append(("mppi_put", cur.run()))
+        self.world.lib.wait_stream(cur)
+        return 0
+
     def mppi_theta_len(self, ctx):
         return 3
 
@@ -76,6 +83,7 @@ def world(monkeypatch):
     c.device = torch.device("cpu")
     c.stream, c.ctx, c._lib = w.lib, 1, Library(w)
     c.batch, c.requires_grad, c.n_inst, c.T, c.m, c.K = False, True, 1, 4, 2, 8
+    c._captured = {}
     c._joined, c._home = False, torch.device("cpu", 0)
     c._off = {k: np.array([0, n]) for k, n in ((_abi.PACKED_STATE, 4), (_abi.PACKED_CONTROLS, 8),
                                                (_abi.PACKED_SAMPLES, 8), (_abi.PACKED_NOISE, 64))}
@@ -158,3 +166,30 @@ def test_a_controller_of_another_device(world, monkeypatch):
     c.iterate(1)
     assert before(second, c._lib.last("mppi_iterate"))
     assert set(asked) == {1}
+
+
+INPUTS = {"mppi_set_state": (4, lambda c, t: c.set_state(t)),
+          "mppi_set_controls": (8, lambda c, t: c.set_controls(t)),
+          "mppi_set_costs": (8, lambda c, t: c.set_costs(t))}
+FORMS = {"as it is": lambda n: torch.zeros(n), "binary64": lambda n: torch.zeros(n).double(),
+         "strided": lambda n: torch.zeros(2 * n)[::2]}
+
+
+@pytest.mark.parametrize("captured", [False, True])
+@pytest.mark.parametrize("form", sorted(FORMS))
+@pytest.mark.parametrize("name", sorted(INPUTS))
+def test_an_input_may_be_written_after_the_call(world, name, form, captured):
+    """What the caller's stream does next, such as reusing the tensor's memory,
+    follows the read (and the conversion before it)."""
+    n, call = INPUTS[name]
+    c, t = world.ctl, FORMS[form](n)
+    made = world.cur.run()
+    world.capturing = captured
+    c.iterate(5)
+    call(c, t)
+    read = c._lib.last(name if captured else "mppi_put")
+    long = c._lib.last("mppi_iterate")
+    assert before(made, read) and before(long, read)
+    assert before(read, world.cur.run())
+    c.iterate(1)
+    assert before(read, c._lib.last("mppi_iterate"))

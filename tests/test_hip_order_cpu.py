@@ -148,6 +148,114 @@ def case_other_device_stream(b):
     assert before(first, copy) and before(copy, last)
 
 
+def case_put(b):
+    """mppi_put reads on the caller's stream, after the context's work and before
+    what either stream is given next; on any stream, of any device."""
+    for dev, mine in ((0, None), (0, b.hip.model_stream(0)), (1, None), (1, b.hip.model_stream(1))):
+        s = b.hip.model_stream(dev)
+        ctx = b.context(s)
+        lib, cur = (dev, b.hip.model_id(s)), (dev, b.hip.model_id(mine))
+        for what in (b.abi.PACKED_STATE, b.abi.PACKED_CONTROLS, b.abi.PACKED_SAMPLES):
+            b.ok(b.L.mppi_sample(ctx))
+            n = b.mark()
+            b.ok(b.L.mppi_put(ctx, what, b.floats, mine))
+            b.ok(b.L.mppi_sample(ctx))
+            new = b.log().ops[n:]
+            copy = [o for o in new if o[1] == cur]
+            assert len(copy) == 1
+            assert before(b.log().ops[n - 1], copy[0]) and before(copy[0], new[-1])
+            assert new[-1][1] == lib
+        b.L.mppi_destroy(ctx)
+    assert b.hip.model_current() == 0
+
+
+# everything that gives a context work
+CALLS = {
+    "set_state": lambda b, c: b.L.mppi_set_state(c, b.floats),
+    "set_controls": lambda b, c: b.L.mppi_set_controls(c, b.floats),
+    "set_costs": lambda b, c: b.L.mppi_set_costs(c, b.floats),
+    "set_iteration": lambda b, c: b.L.mppi_set_iteration(c, 3),
+    "shift": lambda b, c: b.L.mppi_shift(c, 1, 0),
+    "sample": lambda b, c: b.L.mppi_sample(c),
+    "rollout": lambda b, c: b.L.mppi_rollout(c),
+    "update": lambda b, c: b.L.mppi_update(c),
+    "iterate": lambda b, c: b.L.mppi_iterate(c, 1),
+    "iterate_graph": lambda b, c: b.L.mppi_iterate(c, 3),
+    "get_controls": lambda b, c: b.L.mppi_get_controls(c, b.floats),
+    "get_costs": lambda b, c: b.L.mppi_get_debug(c, b.abi.DEBUG_COSTS, b.floats),
+    "get_noise": lambda b, c: b.L.mppi_get_debug(c, b.abi.DEBUG_NOISE, b.floats),
+    "get_weights": lambda b, c: b.L.mppi_get_debug(c, b.abi.DEBUG_WEIGHTS, b.floats),
+    "get_stats": lambda b, c: b.L.mppi_get_debug(c, b.abi.DEBUG_STATS, b.floats),
+}
+
+
+def put_follows(b, ctx, lib, names):
+    for name in names:
+        # the null stream is ordered after the context, then the context gets work
+        b.ok(b.L.mppi_release_stream(ctx, None))
+        b.ok(CALLS[name](b, ctx))
+        work = b.log().on(lib)[-1]
+        b.ok(b.L.mppi_put(ctx, b.abi.PACKED_CONTROLS, b.floats, None))
+        copy = b.log().on((0, 0))[-1]
+        assert before(work, copy), name
+        # a second array straight after it need not wait again, but may not race
+        b.ok(b.L.mppi_put(ctx, b.abi.PACKED_STATE, b.floats, None))
+        assert before(work, b.log().on((0, 0))[-1]), name
+
+
+def case_put_after_every_call(b):
+    s = b.hip.model_stream(0)
+    ctx = b.context(s)
+    b.ok(b.L.mppi_set_state(ctx, b.floats))
+    b.ok(b.L.mppi_sample(ctx))
+    b.ok(b.L.mppi_rollout(ctx))
+    put_follows(b, ctx, (0, b.hip.model_id(s)), CALLS)
+
+
+def case_put_after_every_call_of_a_batch(b):
+    s = b.hip.model_stream(0)
+    ctx = b.context(s, batch=3)
+    b.ok(b.L.mppi_set_state(ctx, b.floats))
+    b.ok(b.L.mppi_sample(ctx))
+    b.ok(b.L.mppi_rollout(ctx))
+    put_follows(b, ctx, (0, b.hip.model_id(s)), CALLS)
+
+
+def case_put_with_gradients(b):
+    s = b.hip.model_stream(0)
+    ctx = b.context(s, grad=True)
+    lib = (0, b.hip.model_id(s))
+    b.ok(b.L.mppi_set_state(ctx, b.floats))
+    put_follows(b, ctx, lib, ["sample", "rollout", "update", "iterate"])
+    b.ok(b.L.mppi_iterate(ctx, 1))
+    for call in (lambda: b.L.mppi_backward(ctx, b.floats, b.floats),
+                 lambda: b.L.mppi_set_theta(ctx, (C.c_float * 6)(*[1.0] * 6))):
+        b.ok(b.L.mppi_release_stream(ctx, None))
+        b.ok(call())
+        work = b.log().on(lib)[-1]
+        b.ok(b.L.mppi_put(ctx, b.abi.PACKED_CONTROLS, b.floats, None))
+        assert before(work, b.log().on((0, 0))[-1])
+
+
+def case_put_from_two_streams(b):
+    """The null stream, then another: each copy follows the one before."""
+    s, mine = b.hip.model_stream(0), b.hip.model_stream(0)
+    ctx = b.context(s)
+    for a, c in ((None, mine), (mine, None)):
+        b.ok(b.L.mppi_put(ctx, b.abi.PACKED_STATE, b.floats, a))
+        first = b.log().ops[-1]
+        b.ok(b.L.mppi_put(ctx, b.abi.PACKED_STATE, b.floats, c))
+        assert before(first, b.log().ops[-1])
+
+
+def case_put_refuses(b):
+    ctx = b.context(b.hip.model_stream(0))
+    for what, src in ((b.abi.PACKED_NOISE, b.floats), (7, b.floats), (0, None)):
+        assert b.L.mppi_put(ctx, what, src, None) == -1
+    assert b.L.mppi_put(None, 0, b.floats, None) == -1
+    assert b.mark() == 0
+
+
 CASES = {n[5:]: f for n, f in list(globals().items()) if n.startswith("case_")}
 
 
