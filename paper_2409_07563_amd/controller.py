@@ -37,8 +37,13 @@ from . import _abi
 from ._abi import check, lib
 
 
+def _stream_handle(device: int) -> int:
+    return torch.cuda.current_stream(device).cuda_stream
+
+
 # handle of torch's current stream on a device, without making a Stream object
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# where this torch has a function for it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_handle)
 
 
 def _fptr(a: np.ndarray):

@@ -2,6 +2,7 @@
 of two streams (the library's and torch's current one) that keeps, for every
 operation, what is certain to have run before it."""
 import contextlib
+import importlib.util
 import types
 
 import numpy as np
@@ -193,3 +194,15 @@ def test_an_input_may_be_written_after_the_call(world, name, form, captured):
     assert before(read, world.cur.run())
     c.iterate(1)
     assert before(read, c._lib.last("mppi_iterate"))
+
+
+def test_a_torch_without_the_raw_stream_function(monkeypatch):
+    """The package loads, and takes the handle from the current stream."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream",
+                        lambda device: types.SimpleNamespace(cuda_stream=100 + device))
+    spec = importlib.util.spec_from_file_location("paper_2409_07563_amd._controller_again",
+                                                  controller.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._raw_stream(1) == 101
