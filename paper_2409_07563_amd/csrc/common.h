@@ -98,7 +98,8 @@ struct NoiseJob {
 constexpr int kXcds = 8, kGroupSamples = 256;
 // sample groups, filled up to a multiple of the XCDs (empty groups do nothing)
 inline int padded_groups(int K) {
-  return (K + kXcds * kGroupSamples - 1) / (kXcds * kGroupSamples) * kXcds;
+  constexpr int64_t kRound = int64_t{kXcds} * kGroupSamples;
+  return static_cast<int>((K + kRound - 1) / kRound) * kXcds;
 }
 // Workgroup b of a launch with `per` workgroups per group, as group * per + its
 // number in the group: group g runs on XCD g mod 8.

@@ -215,7 +215,7 @@ __device__ __forceinline__ void emit_call4(uint32_t key0, uint32_t key1, uint32_
     const int n = 4 * c + s;
     if (n >= TM) continue;
     float* row = eps + static_cast<int64_t>(n) * ldk + k;
-    if (k + 4 <= K) {
+    if (K - k >= 4) {
       *reinterpret_cast<float4*>(row) = float4{z[0][s], z[1][s], z[2][s], z[3][s]};
     } else {
 #pragma unroll

@@ -1,8 +1,8 @@
 /* A model of the HIP runtime for tests without a GPU: devices, streams and
  * events, no work.  Loaded before libmppi.so (dlopen with RTLD_GLOBAL), so that
  * the library's calls come here.  Every call on a stream is a line of the log:
- *   launch DEV STREAM | copy DEV STREAM DST SRC | record EVENT DEV STREAM |
- *   wait DEV STREAM EVENT
+ *   launch DEV STREAM GRIDX GRIDY GRIDZ THREADS | copy DEV STREAM DST SRC |
+ *   record EVENT DEV STREAM | wait DEV STREAM EVENT
  * Stream 0 is the null stream of the device that is current at the call.  What
  * HIP refuses is refused: an event recorded on a stream of another device. */
 #include <stdarg.h>
@@ -80,8 +80,8 @@ int hipMemsetAsync(void* d, int v, size_t n, void* s) {
   return 0;
 }
 int hipLaunchKernel(const void* fn, dim3 g, dim3 b, void** args, size_t lds, void* s) {
-  (void)fn; (void)g; (void)b; (void)args; (void)lds;
-  line("launch %d %d\n", dev_of(s), id_of(s));
+  (void)fn; (void)args; (void)lds;
+  line("launch %d %d %u %u %u %u\n", dev_of(s), id_of(s), g.x, g.y, g.z, b.x * b.y * b.z);
   return 0;
 }
 int hipFuncSetAttribute(const void* fn, int a, int v) { (void)fn; (void)a; (void)v; return 0; }

@@ -1,4 +1,4 @@
-"""The library's stream ordering against a model of the HIP runtime with several
+"""The library's stream ordering and the grids of its largest launches against a model of the HIP runtime with several
 devices (tests/hip_model.c), in a process of its own without torch."""
 import ctypes as C
 import importlib.util
@@ -65,6 +65,7 @@ class Bench:
         self.abi = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(self.abi)
         self.L, self.keep = self.abi.lib(), []
+        self.floats = C.create_string_buffer(1 << 20)
 
     def context(self, stream, batch=0, grad=False):
         """A double-integrator context (or a batch of them; grad: a bicycle with
@@ -94,7 +95,6 @@ class Bench:
             self.ok(self.L.mppi_create_batch(cfg, par, n, at, size, stream, C.byref(ctx)))
         else:
             self.ok(self.L.mppi_create(cfg, par, at, size, stream, C.byref(ctx)))
-        self.floats = C.create_string_buffer(1 << 20)
         self.hip.model_clear()
         return ctx
 
@@ -254,6 +254,24 @@ def case_put_refuses(b):
         assert b.L.mppi_put(ctx, what, src, None) == -1
     assert b.L.mppi_put(None, 0, b.floats, None) == -1
     assert b.mark() == 0
+
+
+def case_noise_of_most_samples(b):
+    """mppi_noise up to the last int32 sample count, whose groups are padded to a
+    multiple of 8 (or 1024 samples each): a grid that covers them and that HIP takes."""
+    sigma = (C.c_float * 8)(*[1.0] * 8)
+    for K in (1, 2047, 2049, 2**20, 2**31 - 4096, 2**31 - 2049, 2**31 - 2047, 2**31 - 1024,
+              2**31 - 1022, 2**31 - 256, 2**31 - 4, 2**31 - 1):
+        for T in (1, 3):
+            for ldk in (K, (K + 63) // 64 * 64):
+                n = b.mark()
+                b.ok(b.L.mppi_noise(1, 0, 0, K, T, 2, sigma, b.floats, ldk, None))
+                _, _, _, _, f = b.log().ops[n]
+                gx, threads = int(f[0]), int(f[3])
+                per = [256, 1024] if ldk % 4 == 0 else [256]  # samples per workgroup
+                assert threads == 256 and gx * threads < 2**32, (K, T, ldk, f)
+                assert any(gx * p >= K and (gx - 8) * p < K for p in per), (K, T, ldk, f)
+                assert gx * 256 <= 2**31, (K, T, ldk, f)  # samples are counted in int32
 
 
 CASES = {n[5:]: f for n, f in list(globals().items()) if n.startswith("case_")}
