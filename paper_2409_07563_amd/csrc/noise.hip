@@ -81,7 +81,7 @@ hipError_t launch_noise(uint64_t seed, const uint32_t* d_iteration, uint32_t ite
   const int ny = (ncall + per - 1) / per;
   const auto kernel = wide ? noise_kernel<true, true>
                            : four ? noise_kernel<true, false> : noise_kernel<false, false>;
-  const int nx = wide ? static_cast<int>((int64_t{K} + 1023) / 1024) : padded_groups(K);
+  const int nx = wide ? static_cast<int>((int64_t{K} + 1023) / 1024) : sample_groups(K);
   hipLaunchKernelGGL(kernel, dim3(nx, ny), dim3(256), 0, stream, static_cast<uint32_t>(seed),
                      static_cast<uint32_t>(seed >> 32), d_iteration, iteration, instance, K, TM, m,
                      s, d_eps, ldk, calls, d_sigma_t, mean_sample ? 1 : 0, d_word_out);

@@ -273,7 +273,7 @@ hipError_t launch_rollout(uint32_t dynamics, uint32_t integrator, uint32_t cost,
   }
   const int64_t threads = static_cast<int64_t>(K) * lanes_per_sample;
   int rblocks = static_cast<int>((threads + block - 1) / block);
-  if (next) rblocks = (rblocks + kXcds - 1) / kXcds * kXcds;  // the noise starts at XCD 0
+  if (next) rblocks = blocks_before_job(rblocks, K, block);
   NoiseJob job{};
   int blocks = rblocks;
   if (next) {

@@ -392,12 +392,12 @@ hipError_t launch_rollout_scan(uint32_t dynamics, uint32_t integrator, uint32_t 
   // 20.3, K 9000 24.7 | 21.8, K 16384 28.5 | 30.8; T 200: K 3001 21.0 | 19.6,
   // K 8192 30.0 | 32.0.
   const int64_t noise_bytes = int64_t{4} * ldk * T * 2;
-  const bool grouped = K >= 2048 && noise_bytes <= int64_t{10} << 20;
+  const bool grouped = K >= 2048 && groups_fill_xcds(K) && noise_bytes <= int64_t{10} << 20;
   const int per = grouped ? kGroupSamples * lanes / block : 0;
   const int64_t threads = static_cast<int64_t>(K) * lanes;
   int rblocks = static_cast<int>((threads + block - 1) / block);
-  if (grouped) rblocks = padded_groups(K) * per;
-  else if (next) rblocks = (rblocks + kXcds - 1) / kXcds * kXcds;  // the noise starts at XCD 0
+  if (grouped) rblocks = sample_groups(K) * per;
+  else if (next) rblocks = blocks_before_job(rblocks, K, block);
   NoiseJob job{};
   int blocks = rblocks;
   if (next) {

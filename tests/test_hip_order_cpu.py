@@ -274,6 +274,17 @@ def case_noise_of_most_samples(b):
                 assert gx * 256 <= 2**31, (K, T, ldk, f)  # samples are counted in int32
 
 
+def case_noise_of_few_samples(b):
+    """The groups that fill up the XCDs are at most a third of the launch's own."""
+    sigma = (C.c_float * 8)(*[1.0] * 8)
+    for K in [*range(1, 5000, 37), 2048, 2049, 3001, 8192, 10007]:
+        n = b.mark()
+        b.ok(b.L.mppi_noise(1, 0, 0, K, 40, 2, sigma, b.floats, K, None))
+        gx = int(b.log().ops[n][4][0])
+        groups = -(-K // 256)
+        assert gx == groups or (gx % 8 == 0 and groups < gx <= groups + groups // 3), (K, gx)
+
+
 CASES = {n[5:]: f for n, f in list(globals().items()) if n.startswith("case_")}
 
 
