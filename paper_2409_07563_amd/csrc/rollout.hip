@@ -25,10 +25,15 @@ __global__ __launch_bounds__(kRolloutMaxBlock) void rollout_kernel(
   }
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * Model::M, lds);
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;  // no barrier follows
+  const int kk = blockIdx.x * blockDim.x + threadIdx.x;
+  if (kk - static_cast<int>(threadIdx.x % kWave) >= K) return;  // whole waves; no barrier follows
+  // The last wave's lanes past K repeat sample K - 1: a wave alone on its CU with
+  // at most 32 lanes at work takes longer over its steps than a full one
+  // (quadrotor, K 1 to 32 and 2049 to 2080, T 200: 148 us, else 131).
+  const int k = min(kk, K - 1);
   const RolloutResult r =
       rollout_lane<Model, INTEG, Cost, COUNT>(p, x0, lds_u, eps + k, ldk, T, lds, k < p.n_plain);
+  if (kk >= K) return;
   S[k] = r.cost;
   if constexpr (COUNT) crashes[k] = r.crashes;
 }
