@@ -361,9 +361,9 @@ typedef struct mppi_tuning {
                                dynamics and gradient mode 64 (one wave per 16-sample
                                tile), or 128 / 256 (the tile's MLP split over 2
                                waves, H = 32 and 64, or 4 waves, H = 64, beside
-                               the waves of the bicycle and the cost; by default
-                               the faster form for the number of samples, the
-                               largest in gradient mode) */
+                               the waves of the bicycle and the cost; H / 16 waves,
+                               the default, only as far as that is the faster form
+                               for the number of samples, else one wave) */
   int32_t batch_tile;       /* samples per work tile of a batch context: 64, 128 or 256 */
   int32_t noise_calls;      /* Philox calls per thread and sample of the
                                single-instance noise kernel: 1, 2 or 4 */

@@ -298,7 +298,8 @@ hipError_t launch_weights(const float* d_S, int K, float lambda, const DevState*
 // MLP residual dynamics and the checkpointing forward (rollout_tiles.hip)
 bool rollout_tiles_supported(uint32_t dynamics, uint32_t integrator, uint32_t cost, int hidden);
 // waves: waves per 16-sample tile: 1, or the MLP split over 2 (H = 32, 64)
-// or 4 (H = 64) waves; hipErrorInvalidValue for other combinations
+// or 4 (H = 64) waves where that is the faster form; hipErrorInvalidValue for
+// other combinations
 hipError_t launch_rollout_tiles(uint32_t dynamics, uint32_t integrator, uint32_t cost,
                                 bool accurate_trig, const DevParams& p, const float* d_x0,
                                 const float* d_u, const float* d_eps, int64_t ldk, int K, int T,

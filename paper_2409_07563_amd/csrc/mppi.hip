@@ -949,20 +949,6 @@ mppi_status upload_sample_tiles(mppi_ctx* c, int tile) {
   return MPPI_OK;
 }
 
-// Whether the MLP rollout takes one wave per 16-sample tile although the split
-// form exists (the costs are the same bit for bit).  A split tile's time adds up
-// over the tiles of a CU, while four one-wave tiles run side by side on its four
-// SIMDs.  Measured at T = 100 (us, split against one wave, for 2, 3, 4 and 6 tiles
-// per CU): H = 64 137/244, 203/244, 260/245, 385/450; H = 32 90/128, 106/128,
-// 130/128, 191/206; bfloat16 products H = 64 89/119, 131/120, 167/121, 245/209;
-// H = 32 69/82, 82/82, 95/83, 140/132.  Gradient mode keeps the split form, which
-// its reverse sweep shares.
-bool one_wave_tiles(const Instance& I) {
-  constexpr int kCus = 256;
-  const int per_cu = ((I.K + 15) / 16 + kCus - 1) / kCus;
-  return !I.grad && (bf16_of(&I.cfg) ? per_cu >= 3 : per_cu % 4 == 0);
-}
-
 mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n_inst, bool batch,
                        void* d_workspace, size_t workspace_bytes, void* hip_stream,
                        mppi_ctx** out) {
@@ -1135,8 +1121,8 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
   const bool tiles = I0.hidden || I0.grad;
   c->tune.lanes_per_sample = tiles ? 16 : (batch ? 1 : I0.lanes);
   // MLP dynamics: the tile's MLP split over H/16 waves where that form exists
-  // and is the faster one
-  c->tune.rollout_block = I0.hidden >= 32 && !one_wave_tiles(I0) ? 4 * I0.hidden : 64;
+  // (and is the faster one: launch_rollout_tiles)
+  c->tune.rollout_block = I0.hidden >= 32 ? 4 * I0.hidden : 64;
   c->tune.batch_tile = kBatchMaxTile;
   c->tune.noise_calls = 1;
   c->tune.rollout_form = MPPI_ROLLOUT_FUSED;

@@ -10,6 +10,7 @@
 // Checkpoints (optional): the state and the compensation terms of the
 // positions at t = 0, c, 2c, ... are stored as ckpt[s][7][ldk], so the
 // adjoint can rebuild each segment bit for bit.
+#include <algorithm>
 #include <type_traits>
 
 #include "mlp.h"
@@ -19,10 +20,17 @@ namespace mppi {
 
 constexpr int kTile = 16;
 constexpr int kCkptWords = 7;
+constexpr int kCus = 256;
+// One-wave tiles share a workgroup from more than two tiles per CU on: the
+// dispatcher places single waves by the SIMDs' turn, which after another launch
+// puts two on one SIMD and none on the next (H = 64, T = 100, 4 tiles per CU, the
+// rollout inside an iteration: 464 us; four waves of a workgroup get a SIMD each:
+// 246, as alone).
+constexpr int kTilesPerGroup = 4;
 
 // BF: the MLP's products on bfloat16 operands (mlp::WeightsBf)
 template <int MT, int INTEG, class Cost, bool FAST, bool BF>
-__global__ __launch_bounds__(kWave) void rollout_tile_kernel(
+__global__ __launch_bounds__(kWave * kTilesPerGroup) void rollout_tile_kernel(
     DevParams p, const float* __restrict__ x0, const float* __restrict__ u,
     const float* __restrict__ eps, int64_t ldk, int K, int T, float* __restrict__ S,
     float* __restrict__ ckpt, int ckpt_every) {
@@ -30,8 +38,11 @@ __global__ __launch_bounds__(kWave) void rollout_tile_kernel(
   constexpr int N = Model::N, M = Model::M;
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * M, lds);
-  const int lane = threadIdx.x, n = lane % kTile, g = lane / kTile;
-  const int k = blockIdx.x * kTile + n;
+  const int lane = threadIdx.x % kWave, n = lane % kTile, g = lane / kTile;
+  const int tile = __builtin_amdgcn_readfirstlane(
+      static_cast<int>((blockIdx.x * blockDim.x + threadIdx.x) / kWave));
+  if (tile * kTile >= K) return;  // the whole wave; no barrier follows
+  const int k = tile * kTile + n;
   const bool live = k < K;
   const bool plain = k < p.n_plain;  // drawn around u (else around zero)
   // v = mean u + eps: an unconditional load and one FMA (mean u + eps is
@@ -153,7 +164,6 @@ __global__ __launch_bounds__(kWave * split_launch_waves(SW)) void rollout_tile_s
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * M, lds);
   const int lane = threadIdx.x % kWave;
-  constexpr int kCus = 256;
   const int turn = static_cast<int>(blockIdx.x / kCus) & 1;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave) ^ (SW == 2 ? 2 * turn : 0);
   const int n = lane % kTile, g = lane / kTile;
@@ -481,6 +491,40 @@ bool rollout_tiles_supported(uint32_t dynamics, uint32_t integrator, uint32_t co
   return select_tile(dynamics, integrator, cost, false, hidden) != nullptr;
 }
 
+namespace {
+
+// How many of the first tiles run one wave each; the split form takes the rest
+// (the costs are the same bit for bit).  A split tile's time adds up over the
+// tiles of a CU, while four one-wave tiles run side by side on its SIMDs: with H = 64
+// a round of four per CU is the faster so, and what is left over is split while that
+// is short.  With H = 32 two or three one-wave tiles share a SIMD at little cost,
+// so all tiles or none.  An iteration, T = 100, us, split | one wave:
+//   H = 64, 1 to 4 tiles per CU (K 4096 each): 90 145 215 294 | 250 256 260 263;
+//     5, 6, 8: 388 437 578 | 469 470 475, a round and the rest split 342 396 475
+//   H = 64, bfloat16: 66 100 143 203 | 126 132 137 137; 5, 6, 8: 252 283 362 |
+//     234 235 238, a round and the rest split 203 236 238 (T = 30, 6: 83 and 87)
+//   H = 32, 1 to 12: 69 100 132 144 194 229 260 292 323 351 378 409 |
+//     135 139 144 144 231 231 233 235 330 332 335 336
+//   H = 32, bfloat16: 61 78 97 107 146 167 188 208 230 250 271 291 |
+//     90 95 99 100 154 154 156 157 215 217 220 221
+int one_wave_tiles(int hidden, int waves, bool bf, int tiles) {
+  if (waves == 1) return tiles;
+  if (hidden == 64 && waves == 4) {
+    constexpr int kRound = 4 * kCus;
+    const int rest = tiles % kRound;
+    const int limit = !bf ? 3 : tiles < kRound ? 2 : 1;  // tiles per CU
+    return rest > limit * kCus ? tiles : tiles - rest;
+  }
+  if (hidden == 32) {
+    const int per_cu = (tiles + kCus - 1) / kCus;
+    const bool one_over = per_cu % 4 == 1 && per_cu < (bf ? 8 : 12);
+    return per_cu >= 4 && !one_over ? tiles : 0;
+  }
+  return 0;
+}
+
+}  // namespace
+
 hipError_t launch_rollout_tiles(uint32_t dynamics, uint32_t integrator, uint32_t cost,
                                 bool accurate_trig, const DevParams& p, const float* d_x0,
                                 const float* d_u, const float* d_eps, int64_t ldk, int K, int T,
@@ -489,24 +533,37 @@ hipError_t launch_rollout_tiles(uint32_t dynamics, uint32_t integrator, uint32_t
   // the split forms: H = 32 over 2 waves; H = 64 over 2 or 4 waves
   const bool mlp = dynamics == MPPI_DYN_BICYCLE_MLP;
   const bool bf = mlp && p.mlp_bf != nullptr;  // BF16 products
-  TileFn fn = nullptr;
-  if (waves == 1) fn = select_tile(dynamics, integrator, cost, accurate_trig, p.mlp_hidden, bf);
-  else if (mlp && p.mlp_hidden == 64 && waves == 4) fn = pick_split<4, 4>(integrator, cost, accurate_trig, bf);
-  else if (mlp && p.mlp_hidden == 64 && waves == 2) fn = pick_split<4, 2>(integrator, cost, accurate_trig, bf);
-  else if (mlp && p.mlp_hidden == 32 && waves == 2) fn = pick_split<2, 2>(integrator, cost, accurate_trig, bf);
-  if (!fn || (d_ckpt && ckpt_every < 1)) return hipErrorInvalidValue;
+  const TileFn one = select_tile(dynamics, integrator, cost, accurate_trig, p.mlp_hidden, bf);
+  TileFn split = nullptr;
+  if (mlp && p.mlp_hidden == 64 && waves == 4) split = pick_split<4, 4>(integrator, cost, accurate_trig, bf);
+  else if (mlp && p.mlp_hidden == 64 && waves == 2) split = pick_split<4, 2>(integrator, cost, accurate_trig, bf);
+  else if (mlp && p.mlp_hidden == 32 && waves == 2) split = pick_split<2, 2>(integrator, cost, accurate_trig, bf);
+  if (!one || (waves != 1 && !split) || (d_ckpt && ckpt_every < 1)) return hipErrorInvalidValue;
   const size_t lds = sizeof(float) * static_cast<size_t>(T) * 2;
-  if (lds > 48 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(lds));
-    if (e != hipSuccess) return e;
-  }
+  // the tiles first .. first + count - 1 in workgroups of `threads` threads for
+  // `per` tiles each
+  auto launch = [&](TileFn fn, int first, int count, int per, int threads) -> hipError_t {
+    if (count < 1) return hipSuccess;
+    if (lds > 48 * 1024) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         static_cast<int>(lds));
+      if (e != hipSuccess) return e;
+    }
+    const int k0 = first * kTile;
+    DevParams q = p;
+    q.n_plain = p.n_plain - k0;
+    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>((count + per - 1) / per)), dim3(threads), lds,
+                       stream, q, d_x0, d_u, d_eps + k0, ldk, std::min(K - k0, count * kTile), T,
+                       d_S + k0, d_ckpt ? d_ckpt + k0 : nullptr, ckpt_every);
+    return hipGetLastError();
+  };
+  const int tiles = (K + kTile - 1) / kTile;
+  const int n1 = one_wave_tiles(p.mlp_hidden, waves, bf, tiles);
+  const int per = n1 > 2 * kCus ? kTilesPerGroup : 1;
+  const hipError_t e = launch(one, 0, n1, per, kWave * per);
   // the split forms' helper waves come on top of the MLP's
-  const int block = kWave * (waves > 1 ? split_launch_waves(waves) : 1);
-  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>((K + kTile - 1) / kTile)), dim3(block), lds,
-                     stream, p, d_x0, d_u, d_eps, ldk, K, T, d_S, d_ckpt, ckpt_every);
-  return hipGetLastError();
+  return e == hipSuccess ? launch(split, n1, tiles - n1, 1, kWave * split_launch_waves(waves)) : e;
 }
 
 }  // namespace mppi

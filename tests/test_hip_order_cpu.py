@@ -67,29 +67,32 @@ class Bench:
         self.L, self.keep = self.abi.lib(), []
         self.floats = C.create_string_buffer(1 << 20)
 
-    def context(self, stream, batch=0, grad=False):
-        """A double-integrator context (or a batch of them; grad: a bicycle with
-        gradients) on a stream of the model."""
+    def context(self, stream, batch=0, grad=False, hidden=0, bf16=False, K=100):
+        """A double-integrator context (or a batch of them; hidden: a bicycle with an
+        MLP residual, grad: a bicycle with gradients) on a stream of the model."""
         abi, n = self.abi, max(1, batch)
         cfg, par = (abi.Config * n)(), (abi.Params * n)()
-        model = "bicycle" if grad else "double_integrator"
-        state = 5 if grad else 4
+        model = "bicycle_mlp" if hidden else "bicycle" if grad else "double_integrator"
+        track = bool(grad or hidden)
+        state = 5 if track else 4
         ref = (C.c_float * (5 * 21))()
+        mlp = (C.c_float * (14 * hidden + hidden**2 + 5))()
         for c, p in zip(cfg, par):
             c.abi_version = abi.ABI_VERSION
-            c.dynamics, c.cost = abi.DYNAMICS[model], abi.COSTS["track" if grad else "quadratic"]
-            c.integrator = abi.INTEGRATORS["rk4" if grad else "euler"]
-            c.num_samples, c.horizon, c.state_dim, c.control_dim = 100, 20, state, 2
+            c.dynamics, c.cost = abi.DYNAMICS[model], abi.COSTS["track" if track else "quadratic"]
+            c.integrator = abi.INTEGRATORS["rk4" if track else "euler"]
+            c.num_samples, c.horizon, c.state_dim, c.control_dim = K, 20, state, 2
             c.dt, c.lam = 0.1, 1.0
             c.sigma[0] = c.sigma[1] = 1.0
-            c.flags = abi.F_REQUIRES_GRAD if grad else 0
+            c.flags = (abi.F_REQUIRES_GRAD if grad else 0) | (abi.F_BF16_MLP if bf16 else 0)
+            p.mlp_hidden, p.mlp = hidden, mlp
             p.wheelbase, p.ref, p.ref_len = 2.5, ref, len(ref)
         size = (self.L.mppi_batch_workspace_bytes(cfg, par, n) if batch
                 else self.L.mppi_workspace_bytes(cfg, par))
         assert size, self.L.mppi_last_error()
         ws = C.create_string_buffer(size + 256)
         at = (C.addressof(ws) + 255) // 256 * 256
-        self.keep += [cfg, par, ref, ws]
+        self.keep = [cfg, par, ref, mlp, ws]
         ctx = C.c_void_p()
         if batch:
             self.ok(self.L.mppi_create_batch(cfg, par, n, at, size, stream, C.byref(ctx)))
@@ -283,6 +286,33 @@ def case_noise_of_few_samples(b):
         gx = int(b.log().ops[n][4][0])
         groups = -(-K // 256)
         assert gx == groups or (gx % 8 == 0 and groups < gx <= groups + groups // 3), (K, gx)
+
+
+def case_mlp_rollout_launches(b):
+    """Every 16-sample tile in one launch or another, and never more than two
+    workgroups per CU of a single wave (which the SIMDs get unevenly)."""
+    s = b.hip.model_stream(0)
+    for hidden in (16, 32, 64):
+        for bf16 in (False, True):
+            for grad in (False, True):
+                for K in (1, 17, 4096, 8192, 8193, 12288, 12289, 16384, 16385, 17000, 20481,
+                          28673, 65536, 65537):
+                    ctx = b.context(s, grad=grad, hidden=hidden, bf16=bf16, K=K)
+                    b.ok(b.L.mppi_set_state(ctx, b.floats))
+                    b.ok(b.L.mppi_sample(ctx))
+                    n = b.mark()
+                    b.ok(b.L.mppi_rollout(ctx))
+                    tiles, low, high = -(-K // 16), 0, 0
+                    launches = [o for o in b.log().ops[n:] if o[0] == "launch"]
+                    for _, _, _, _, f in launches:
+                        groups, threads = int(f[0]), int(f[3])
+                        assert threads != 64 or groups <= 512, (hidden, bf16, K, f)
+                        # a split tile has four waves (H = 32) or eight, else a wave each
+                        most = threads // 64 if threads < 512 else 1
+                        low += groups * (1 if hidden == 32 and threads == 256 else most) - most + 1
+                        high += groups * most
+                    assert 1 <= len(launches) <= 2 and low <= tiles <= high, (hidden, bf16, K)
+                    b.L.mppi_destroy(ctx)
 
 
 CASES = {n[5:]: f for n, f in list(globals().items()) if n.startswith("case_")}
