@@ -939,7 +939,7 @@ __global__ __launch_bounds__(kWave) void adjoint_sweep_kernel(
     DevParams p, const float* __restrict__ u, const float* __restrict__ eps, int64_t ldk, int T,
     const float* __restrict__ ckpt, int c, const BwdItem* __restrict__ list,
     const BwdMeta* __restrict__ meta, float* __restrict__ partial, int64_t ngp, int du_off,
-    mlp::f4* __restrict__ pre, const float* __restrict__ tp, int tp_tiles) {
+    mlp::f4* __restrict__ pre, const float* __restrict__ tp, int tp_tiles, int) {
   using Model = Bicycle<FAST>;
   using L = SweepLds<MT, BF>;
   using f4 = mlp::f4;
@@ -1263,7 +1263,7 @@ __global__ __launch_bounds__(kWave * sweep_launch_waves(SW), MT == 2 ? 4 : 2)
     DevParams p, const float* __restrict__ u, const float* __restrict__ eps, int64_t ldk, int T,
     const float* __restrict__ ckpt, int c, const BwdItem* __restrict__ list,
     const BwdMeta* __restrict__ meta, float* __restrict__ partial, int64_t ngp, int du_off,
-    mlp::f4* __restrict__ pre, const float* __restrict__ tp, int tp_tiles) {
+    mlp::f4* __restrict__ pre, const float* __restrict__ tp, int tp_tiles, int row0) {
   static_assert(MT % SW == 0, "tiles per wave");
   constexpr int TW = MT / SW;
   using f4 = mlp::f4;
@@ -1279,7 +1279,7 @@ __global__ __launch_bounds__(kWave * sweep_launch_waves(SW), MT == 2 ? 4 : 2)
   const int slot = wave < kSweepSlots * SW ? wave / SW : wave - kSweepSlots * SW;
   const int w = wave < kSweepSlots * SW ? wave % SW : helper;
   const int b = static_cast<int>(blockIdx.x);
-  const int rowid = (b / kSweepCus * kSweepSlots + slot) * kSweepCus + b % kSweepCus;
+  const int rowid = row0 + (b / kSweepCus * kSweepSlots + slot) * kSweepCus + b % kSweepCus;
   const SegSel sel = seg_select(rowid, nseg, c, tp_tiles, meta->count);
   const int nunit = nseg * sel.sub;
   const int base = sel.tile * kTileS;
@@ -1901,7 +1901,7 @@ size_t adjoint_lds_bytes(int hidden, int ckpt_every, bool bf) {
 namespace {
 using SweepFn = void (*)(DevParams, const float*, const float*, int64_t, int, const float*, int,
                          const BwdItem*, const BwdMeta*, float*, int64_t, int, mlp::f4*,
-                         const float*, int);
+                         const float*, int, int);
 using TpFn = void (*)(DevParams, const float*, const float*, int64_t, int, const float*, int,
                       const BwdItem*, const BwdMeta*, int, float*, mlp::f4*);
 template <int MT, bool BF = false>
@@ -2027,12 +2027,23 @@ hipError_t launch_adjoint(const DevParams& p, bool accurate_trig, int hidden, co
                        d_eps, ldk, T, d_ckpt, ckpt_every, list, meta, tp, tpbuf, pre);
   }
   const int rows = std::max(tiles, tp * nunit);
-  // the split sweep's workgroup b takes rows 512 (b / 256) + b mod 256 and that + 256
+  // The split sweep's workgroup b takes rows 512 (b / 256) + b mod 256 and that +
+  // 256.  With H = 32 a CU holds two workgroups at a time, and from the third on
+  // they fall on its SIMDs unevenly (every sample weighted, T = 100, 4 tiles per CU
+  // 401 us, 8 in one launch 936): rounds of four tiles per CU in a launch each, the
+  // rows beyond the last whole one with it (8: 787).
   constexpr int kGroup = kSweepSlots * kSweepCus;
-  const int grid = waves == 1 || rows <= kSweepCus ? rows : (rows + kGroup - 1) / kGroup * kSweepCus;
-  hipLaunchKernelGGL(fn, dim3(grid),
-                     dim3(kWave * (waves > 1 ? sweep_launch_waves(waves) : 1)), lds, stream, p, d_u, d_eps, ldk, T,
-                     d_ckpt, ckpt_every, list, meta, partial, s.ngp, du_off, pre, tpbuf, tp);
+  const int round = waves > 1 && hidden == 32 ? 2 * kGroup : rows;
+  for (int row0 = 0; row0 < rows; row0 += round) {
+    const bool last = rows - row0 < 2 * round;
+    const int n = last ? rows - row0 : round;
+    const int grid = waves == 1 || n <= kSweepCus ? n : (n + kGroup - 1) / kGroup * kSweepCus;
+    hipLaunchKernelGGL(fn, dim3(grid),
+                       dim3(kWave * (waves > 1 ? sweep_launch_waves(waves) : 1)), lds, stream, p,
+                       d_u, d_eps, ldk, T, d_ckpt, ckpt_every, list, meta, partial, s.ngp, du_off,
+                       pre, tpbuf, tp, row0);
+    if (last) break;
+  }
   hipLaunchKernelGGL(adjoint_reduce_kernel, dim3((ncols + kReduceCols - 1) / kReduceCols),
                      dim3(kReduceCols * kReduceParts), 0, stream, partial, s.ngp, ngrad, ncols,
                      meta, d_grad, accumulate ? 1 : 0, d_G_acc, tp, nunit);

@@ -315,6 +315,22 @@ def case_mlp_rollout_launches(b):
                     b.L.mppi_destroy(ctx)
 
 
+def case_sweep_launches(b):
+    """H = 32: the reverse sweep's rows in launches of less than two rounds of four
+    tiles per CU, none left out."""
+    s = b.hip.model_stream(0)
+    for K in (100, 4097, 16384, 32752, 32768, 33000, 65536):
+        ctx = b.context(s, grad=True, hidden=32, K=K)
+        b.ok(b.L.mppi_set_state(ctx, b.floats))
+        b.ok(b.L.mppi_iterate(ctx, 1))
+        n = b.mark()
+        b.ok(b.L.mppi_backward(ctx, b.floats, b.floats))
+        grids = [int(o[4][0]) for o in b.log().ops[n:] if o[0] == "launch" and o[4][3] == "384"]
+        tiles = -(-K // 16)
+        assert all(g <= 1024 for g in grids) and 2 * sum(grids) >= tiles, (K, grids)
+        b.L.mppi_destroy(ctx)
+
+
 CASES = {n[5:]: f for n, f in list(globals().items()) if n.startswith("case_")}
 
 
