@@ -1196,11 +1196,39 @@ bool rollout_draws_noise(const mppi_ctx* c) {
 //   T 24: K 32768 13.4 | 14.0; 29.3 | 17.3    T 48: K 65536 32.0 | 27.0; 36.9 | 36.4
 // and 32 lanes while 16 lanes leave SIMDs idle (T 30, K 3001: 5.9 with 16
 // lanes, 6.5 with 32; T 77, K 3001: 8.8 and 8.2).
+// The costs above search cells (circles, or a two-valued costmap's bitmap) at
+// every step, which the lanes share.  Where there are none to search a step is
+// short and the lines lie further out.  An iteration, grouped or one-lane over
+// time-parallel, quadratic cost; a spline with a costmap of many values:
+//   K 64: T 1 7.0/8.1; 7.7/8.9, T 4 7.5/8.2; 8.0/9.0, T 16 10.2/9.1; 10.5/8.8
+//   K 8192: T 8 10.7/11.1; 11.5/11.8, T 16 14.1/12.8; 15.1/13.4
+//   K 16384: T 16 15.7/16.2, T 24 0.95 of it; K 32768: T 24 0.99, 0.98 of it
+//   K 36864: T 128 time-parallel 1.11 of it; 0.87   K 57344: T 100 1.06; 0.95
+//   K 65536: T 48 1.09; 1.03, T 100 1.12; 1.08, T 160 0.80; 0.77
+//   K 98304: T 48 1.21; 1.20, T 100 1.01; 1.00, T 256 1.04; 1.09
+// and with cells K 98304: T 48 1.03, T 64 0.96, K 8192: T 1 11.1/11.7, T 8 0.93.
 int default_scan_lanes(const Instance& I) {
   if (I.hidden || I.grad || (I.cfg.flags & (MPPI_F_ROLLOUT_LANE | MPPI_F_ROLLOUT_QUAD))) return 0;
   const int lanes = I.K <= 1024 || (I.K <= 4096 && I.T > 64) ? 32 : 16;
   if (!rollout_scan_supported(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, I.T, lanes)) return 0;
-  const int min_steps = I.K > 32768 ? 48 : I.K > 16384 ? 24 : I.K > 8192 ? 16 : 1;
+  constexpr int kNever = 1 << 30;
+  const bool cells = uses_circles(I.cfg.cost) ? I.dp.ncirc > 0
+                                              : I.cfg.cost == MPPI_COST_PATH_COSTMAP &&
+                                                    I.dp.map_bits4 >= 0;
+  int min_steps;
+  if (cells)
+    min_steps = I.K > 65536   ? 64
+                : I.K > 32768 ? 48
+                : I.K > 16384 ? 24
+                : I.K > 8192  ? 16
+                : I.K > 4096  ? 6
+                              : 1;
+  else if (I.K <= 32768)
+    min_steps = I.K > 8192 ? 24 : 12;
+  else if (!uses_spline(I.cfg.cost))
+    min_steps = kNever;
+  else
+    min_steps = I.K > 65536 ? kNever : I.K > 57344 ? 160 : 48;
   return I.T >= min_steps ? lanes : 0;
 }
 

@@ -1,7 +1,7 @@
 /* A model of the HIP runtime for tests without a GPU: devices, streams and
  * events, no work.  Loaded before libmppi.so (dlopen with RTLD_GLOBAL), so that
  * the library's calls come here.  Every call on a stream is a line of the log:
- *   launch DEV STREAM GRIDX GRIDY GRIDZ THREADS | copy DEV STREAM DST SRC |
+ *   launch DEV STREAM GRIDX GRIDY GRIDZ THREADS KERNEL | copy DEV STREAM DST SRC |
  *   record EVENT DEV STREAM | wait DEV STREAM EVENT
  * Stream 0 is the null stream of the device that is current at the call.  What
  * HIP refuses is refused: an event recorded on a stream of another device. */
@@ -34,6 +34,9 @@ static void* new_object(int dev) {
   o->id = next++;
   return o;
 }
+
+static struct { const void* fn; char name[512]; } kernel[4096];
+static int kernels;
 
 /* for the test */
 const char* model_log(void) { return log_text; }
@@ -80,8 +83,11 @@ int hipMemsetAsync(void* d, int v, size_t n, void* s) {
   return 0;
 }
 int hipLaunchKernel(const void* fn, dim3 g, dim3 b, void** args, size_t lds, void* s) {
-  (void)fn; (void)args; (void)lds;
-  line("launch %d %d %u %u %u %u\n", dev_of(s), id_of(s), g.x, g.y, g.z, b.x * b.y * b.z);
+  (void)args; (void)lds;
+  const char* name = "?";
+  for (int i = 0; i < kernels; ++i)
+    if (kernel[i].fn == fn) name = kernel[i].name;
+  line("launch %d %d %u %u %u %u %s\n", dev_of(s), id_of(s), g.x, g.y, g.z, b.x * b.y * b.z, name);
   return 0;
 }
 int hipFuncSetAttribute(const void* fn, int a, int v) { (void)fn; (void)a; (void)v; return 0; }
@@ -119,7 +125,10 @@ int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, void** s) {
 void** __hipRegisterFatBinary(const void* data) { (void)data; static void* h; return &h; }
 void __hipRegisterFunction(void** m, const void* f, char* df, const char* n, unsigned t, void* a,
                            void* b, void* c, void* d, int* w) {
-  (void)m; (void)f; (void)df; (void)n; (void)t; (void)a; (void)b; (void)c; (void)d; (void)w;
+  (void)m; (void)df; (void)t; (void)a; (void)b; (void)c; (void)d; (void)w;
+  if (kernels == 4096) abort();
+  kernel[kernels].fn = f;
+  snprintf(kernel[kernels++].name, sizeof kernel[0].name, "%s", n);
 }
 void __hipRegisterVar(void** m, void* v, char* h, char* n, int e, size_t s, int c, int g) {
   (void)m; (void)v; (void)h; (void)n; (void)e; (void)s; (void)c; (void)g;

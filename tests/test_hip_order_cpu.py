@@ -101,6 +101,54 @@ class Bench:
         self.hip.model_clear()
         return ctx
 
+    def bicycle(self, K, T, cost, flags=0):
+        """A bicycle (RK4) context on a stream of the model; cost: "quadratic",
+        "circles" (none: "no_circles"), "map" (two values; more: "values"), "goal"."""
+        abi = self.abi
+        cfg, p = abi.Config(), abi.Params()
+        cfg.abi_version, cfg.dynamics = abi.ABI_VERSION, abi.DYNAMICS["bicycle"]
+        cfg.cost = abi.COSTS[{"quadratic": "quadratic", "circles": "path_circles",
+                              "no_circles": "path_circles", "map": "path_costmap",
+                              "values": "path_costmap", "goal": "goal_circles"}[cost]]
+        cfg.integrator = abi.INTEGRATORS["rk4"]
+        cfg.num_samples, cfg.horizon, cfg.state_dim, cfg.control_dim = K, T, 5, 2
+        cfg.dt, cfg.lam = 0.1, 1.0
+        cfg.sigma[0] = cfg.sigma[1] = 1.0
+        cfg.flags = flags
+        four = (C.c_float * 4)(1.0, 2.0, 3.0, 4.0)
+        ref = (C.c_float * 5)()
+        cells = (C.c_float * 64)(*[float(i if cost == "values" else i % 2) for i in range(64)])
+        p.wheelbase, p.ref, p.ref_len = 2.5, ref, 5
+        p.num_segments, p.knots, p.coef = 1, four, four
+        p.num_circles = 0 if cost == "no_circles" else 2
+        p.cx = p.cy = p.r2 = four
+        p.map_w = p.map_h = 8
+        p.map_res, p.costmap = 1.0, cells
+        size = self.L.mppi_workspace_bytes(cfg, p)
+        assert size, self.L.mppi_last_error()
+        ws = C.create_string_buffer(size + 256) if size < 1 << 28 else None
+        # the model runs nothing, so a large workspace is only an address
+        at = (C.addressof(ws) + 255) // 256 * 256 if ws else 1 << 40
+        self.keep = [cfg, p, four, ref, cells, ws]
+        ctx = C.c_void_p()
+        self.ok(self.L.mppi_create(cfg, p, at, size, self.hip.model_stream(0), C.byref(ctx)))
+        self.ok(self.L.mppi_set_state(ctx, self.floats))
+        self.ok(self.L.mppi_sample(ctx))
+        return ctx
+
+    def rollout_kernel(self, ctx):
+        """(kernel, lanes of the time-parallel form, threads) of the next rollout."""
+        n = self.mark()
+        self.ok(self.L.mppi_rollout(ctx))
+        f = self.log().ops[n][4]
+        name = f[4]
+        if "rollout_bicycle_scan_kernel" in name:
+            return "scan", int(name.split("Li")[-1].split("E")[0]), int(f[3])
+        if "rollout_bicycle_group_kernel" in name:
+            return "group", int(name.split("Li")[-1].split("E")[0]), int(f[3])
+        assert "rollout_kernel" in name, name
+        return "lane", 1, int(f[3])
+
     def ok(self, status):
         assert status == 0, self.L.mppi_last_error()
 
@@ -328,6 +376,26 @@ def case_sweep_launches(b):
         grids = [int(o[4][0]) for o in b.log().ops[n:] if o[0] == "launch" and o[4][3] == "384"]
         tiles = -(-K // 16)
         assert all(g <= 1024 for g in grids) and 2 * sum(grids) >= tiles, (K, grids)
+        b.L.mppi_destroy(ctx)
+
+
+def case_default_rollout(b):
+    """Where the time-parallel rollout is the default: with cells to search, and
+    further out without."""
+    want = {  # (cost, K, T): whether time-parallel
+        ("circles", 64, 1): True, ("circles", 8192, 5): False, ("circles", 8192, 6): True,
+        ("map", 16384, 16): True, ("goal", 32768, 24): True, ("circles", 65536, 48): True,
+        ("circles", 65537, 48): False, ("map", 65537, 64): True, ("goal", 70000, 64): True,
+        ("quadratic", 64, 11): False, ("quadratic", 64, 12): True, ("values", 8192, 12): True,
+        ("no_circles", 8193, 23): False, ("no_circles", 8193, 24): True,
+        ("quadratic", 32768, 24): True, ("quadratic", 32769, 200): False,
+        ("values", 57344, 48): True, ("values", 57345, 159): False,
+        ("no_circles", 57345, 160): True, ("values", 65537, 250): False,
+        ("circles", 512, 257): False,
+    }
+    for (cost, K, T), scan in want.items():
+        ctx = b.bicycle(K, T, cost)
+        assert (b.rollout_kernel(ctx)[0] == "scan") == scan, (cost, K, T)
         b.L.mppi_destroy(ctx)
 
 
