@@ -385,8 +385,8 @@ def run_single(args, wl, update_forms: bool = False, autotune_reps: int = 30) ->
                        max(1, args.warmup // 5)) / 10
     achieved = ops_step * steps_per_iter / t_roll
     split = tune["rollout_form"] == 1
-    scan = tune["rollout_form"] == 2
     lanes = tune["lanes_per_sample"]
+    scan = tune["rollout_form"] == 2 or lanes == 0  # 0: the library's choice
     kernel = ("di_iteration_kernel (the whole iteration)" if fused else
               "split_dynamics + split_cost" if split else
               "rollout_bicycle_scan_kernel" if scan else

@@ -312,11 +312,11 @@ mppi_status mppi_offsets(const mppi_ctx* ctx, int32_t what, int64_t* host_offset
  * T <= 256 (not for gradient mode), with lanes_per_sample 16 and
  * rollout_block threads per workgroup.  Equally accurate: the positions are
  * summed with compensation; only the rounding order differs.
- * Until mppi_set_tuning or mppi_autotune is called, a context for which the
- * form exists and neither MPPI_F_ROLLOUT_LANE nor _QUAD is set also runs it
- * (16 or 32 lanes, 256 threads) where it is the faster one: all but short
- * horizons with many samples.  mppi_get_tuning then reports the fused form
- * that these calls start from; setting it, even unchanged, selects it. */
+ * A context for which the form exists and neither MPPI_F_ROLLOUT_LANE nor _QUAD
+ * is set is created with lanes_per_sample 0 where it is the faster one (all but
+ * short horizons with many samples, and costs without circles or a two-valued
+ * costmap for many samples): it runs this form with 16 or 32 lanes and 256 threads
+ * until other lanes_per_sample are set, whatever the other fields. */
 enum { MPPI_ROLLOUT_FUSED = 0, MPPI_ROLLOUT_SPLIT = 1, MPPI_ROLLOUT_SCAN = 2 };
 /* Steps (a3)-(a6) (Algorithm 1, Eq. mppi_update_rule):
  *  TWO_PASS: a weights step in one workgroup writes the weights, then one
@@ -356,7 +356,9 @@ typedef struct mppi_tuning {
                                instance: RK4 stages across a quad, the running cost
                                shared by the lanes; 16 also in the scan form: the
                                horizon across the lanes); 16 for MLP dynamics and
-                               gradient mode (fixed) */
+                               gradient mode (fixed); 0 in the fused form, for a
+                               context created so: the time-parallel form as above,
+                               rollout_block then being without effect */
   int32_t rollout_block;    /* threads per rollout workgroup: 64, 128 or 256; for MLP
                                dynamics and gradient mode 64 (one wave per 16-sample
                                tile), or 128 / 256 (the tile's MLP split over 2

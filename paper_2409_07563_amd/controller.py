@@ -349,7 +349,8 @@ class Controller:
     def set_tuning(self, **shape) -> None:
         """Change launch shapes (lanes_per_sample, rollout_block, batch_tile,
         noise_calls, rollout_form, cost_waves, update_form, batch_form,
-        adjoint_tiles); the others keep their values."""
+        adjoint_tiles); the others keep their values (lanes_per_sample 0: the
+        library's choice of the rollout)."""
         t = _abi.Tuning()
         check(self._lib.mppi_get_tuning(self.ctx, C.byref(t)))
         for k, v in shape.items():

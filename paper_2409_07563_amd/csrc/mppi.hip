@@ -650,7 +650,7 @@ struct mppi_ctx {
   // whether its noise was drawn ahead)
   std::map<int64_t, hipGraphExec_t> graphs;
   mppi_tuning tune{};                     // launch shapes (lanes: instance 0's choice)
-  bool tuned = false;                     // mppi_set_tuning or mppi_autotune chose them
+  int fused_lanes = 1;                    // instance 0's lanes as created
   // ordering with the caller's streams (mppi_wait_stream, mppi_release_stream):
   // events made on first use, on the context's device
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
@@ -949,6 +949,69 @@ mppi_status upload_sample_tiles(mppi_ctx* c, int tile) {
   return MPPI_OK;
 }
 
+// Lanes per sample of the time-parallel rollout (256 threads per workgroup) where
+// the choice is the library's (lanes_per_sample 0), 0 where the grouped or one-lane
+// rollout is the faster one.  Time-parallel, a step's arithmetic is
+// the same but the chain is T / 16 or T / 32 steps instead of T; it loses only
+// where the samples alone fill the chip and the horizon is too short to pay
+// for the prefix sums.  Rollout, us, circles cost (grouped or one-lane | 16
+// lanes | 32 lanes):
+//   T  30: K 512 11.5 | 6.6 | 5.4, K 32768 15.6 | 14.7 | 22.0, K 65536 21.1 | 24.2 | 39.3
+//   T 100: K 512 25.9 | 10.2 | 7.5, K 8192 28.5 | 12.1 | 12.2, K 65536 58.3 | 43.3 | 55.5
+//   T 200: K 3001 50.2 | 16.1 | 13.3, K 8192 54.7 | 20.2 | 21.1, K 65536 113.7 | 76.6 | 104.1
+// Where the lines lie (grouped or one-lane | time-parallel, circles; costmap):
+//   T  8: K  8192  6.8 |  6.0;  9.4 |  6.9    K 16384  6.9 |  8.0;  9.5 |  9.3
+//   T 16: K 16384  8.7 |  8.2; 11.5 |  9.5    K 32768 10.6 | 12.4; 23.6 | 14.5
+//   T 24: K 32768 13.4 | 14.0; 29.3 | 17.3    T 48: K 65536 32.0 | 27.0; 36.9 | 36.4
+// and 32 lanes while 16 lanes leave SIMDs idle (T 30, K 3001: 5.9 with 16
+// lanes, 6.5 with 32; T 77, K 3001: 8.8 and 8.2).
+// The costs above search cells (circles, or a two-valued costmap's bitmap) at
+// every step, which the lanes share.  Where there are none to search a step is
+// short and the lines lie further out.  An iteration, grouped or one-lane over
+// time-parallel, quadratic cost; a spline with a costmap of many values:
+//   K 64: T 1 7.0/8.1; 7.7/8.9, T 4 7.5/8.2; 8.0/9.0, T 16 10.2/9.1; 10.5/8.8
+//   K 8192: T 8 10.7/11.1; 11.5/11.8, T 16 14.1/12.8; 15.1/13.4
+//   K 16384: T 16 15.7/16.2, T 24 0.95 of it; K 32768: T 24 0.99, 0.98 of it
+//   K 36864: T 128 time-parallel 1.11 of it; 0.87   K 57344: T 100 1.06; 0.95
+//   K 65536: T 48 1.09; 1.03, T 100 1.12; 1.08, T 160 0.80; 0.77
+//   K 98304: T 48 1.21; 1.20, T 100 1.01; 1.00, T 256 1.04; 1.09
+// and with cells K 98304: T 48 1.03, T 64 0.96, K 8192: T 1 11.1/11.7, T 8 0.93.
+int default_scan_lanes(const Instance& I) {
+  if (I.hidden || I.grad || (I.cfg.flags & (MPPI_F_ROLLOUT_LANE | MPPI_F_ROLLOUT_QUAD))) return 0;
+  const int lanes = I.K <= 1024 || (I.K <= 4096 && I.T > 64) ? 32 : 16;
+  if (!rollout_scan_supported(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, I.T, lanes)) return 0;
+  constexpr int kNever = 1 << 30;
+  const bool cells = uses_circles(I.cfg.cost) ? I.dp.ncirc > 0
+                                              : I.cfg.cost == MPPI_COST_PATH_COSTMAP &&
+                                                    I.dp.map_bits4 >= 0;
+  int min_steps;
+  if (cells)
+    min_steps = I.K > 65536   ? 64
+                : I.K > 32768 ? 48
+                : I.K > 16384 ? 24
+                : I.K > 8192  ? 16
+                : I.K > 4096  ? 6
+                              : 1;
+  else if (I.K <= 32768)
+    min_steps = I.K > 8192 ? 24 : 12;
+  else if (!uses_spline(I.cfg.cost))
+    min_steps = kNever;
+  else
+    min_steps = I.K > 65536 ? kNever : I.K > 57344 ? 160 : 48;
+  return I.T >= min_steps ? lanes : 0;
+}
+
+// Threads per workgroup of the fused rollout as created: with 64 the dispatcher
+// puts waves on SIMDs that hold one while others are empty, with 256 every CU's
+// four SIMDs get one each.  One iteration, 64 | 256 threads, us: quadrotor K 65536
+// T 200 271 | 236, K 32768 T 200 196 | 190, K 10007 T 200 147 | 145; double
+// integrator K 65536 T 200 99 | 97; bicycle (one lane) K 65536 T 30 47 | 42.  Below,
+// for the shorter steps, one wave per CU is the better: double integrator K 16384
+// T 100 17.4 and 19.1 for the rollout.
+int default_rollout_block(const Instance& I) {
+  return I.lanes == 1 && (I.K >= 32768 || I.cfg.dynamics == MPPI_DYN_QUADROTOR) ? 256 : 64;
+}
+
 mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n_inst, bool batch,
                        void* d_workspace, size_t workspace_bytes, void* hip_stream,
                        mppi_ctx** out) {
@@ -1119,10 +1182,14 @@ mppi_status create_ctx(const mppi_config* cfgs, const mppi_params* params, int n
   // would leave most SIMDs idle
   const Instance& I0 = c->inst[0];
   const bool tiles = I0.hidden || I0.grad;
-  c->tune.lanes_per_sample = tiles ? 16 : (batch ? 1 : I0.lanes);
+  c->fused_lanes = I0.lanes;
+  c->tune.lanes_per_sample =
+      tiles ? 16 : batch ? 1 : default_scan_lanes(I0) ? 0 : I0.lanes;
   // MLP dynamics: the tile's MLP split over H/16 waves where that form exists
   // (and is the faster one: launch_rollout_tiles)
-  c->tune.rollout_block = I0.hidden >= 32 ? 4 * I0.hidden : 64;
+  c->tune.rollout_block = I0.hidden >= 32                          ? 4 * I0.hidden
+                          : tiles || batch || default_scan_lanes(I0) ? 64
+                                                                     : default_rollout_block(I0);
   c->tune.batch_tile = kBatchMaxTile;
   c->tune.noise_calls = 1;
   c->tune.rollout_form = MPPI_ROLLOUT_FUSED;
@@ -1180,72 +1247,6 @@ bool rollout_draws_noise(const mppi_ctx* c) {
   return !c->batch && !(I.hidden || I.grad) && c->tune.rollout_form != MPPI_ROLLOUT_SPLIT;
 }
 
-// Lanes per sample of the time-parallel rollout (256 threads per workgroup) of
-// a context whose launch shapes nobody has chosen, 0 where the grouped or
-// one-lane rollout is the faster one.  Time-parallel, a step's arithmetic is
-// the same but the chain is T / 16 or T / 32 steps instead of T; it loses only
-// where the samples alone fill the chip and the horizon is too short to pay
-// for the prefix sums.  Rollout, us, circles cost (grouped or one-lane | 16
-// lanes | 32 lanes):
-//   T  30: K 512 11.5 | 6.6 | 5.4, K 32768 15.6 | 14.7 | 22.0, K 65536 21.1 | 24.2 | 39.3
-//   T 100: K 512 25.9 | 10.2 | 7.5, K 8192 28.5 | 12.1 | 12.2, K 65536 58.3 | 43.3 | 55.5
-//   T 200: K 3001 50.2 | 16.1 | 13.3, K 8192 54.7 | 20.2 | 21.1, K 65536 113.7 | 76.6 | 104.1
-// Where the lines lie (grouped or one-lane | time-parallel, circles; costmap):
-//   T  8: K  8192  6.8 |  6.0;  9.4 |  6.9    K 16384  6.9 |  8.0;  9.5 |  9.3
-//   T 16: K 16384  8.7 |  8.2; 11.5 |  9.5    K 32768 10.6 | 12.4; 23.6 | 14.5
-//   T 24: K 32768 13.4 | 14.0; 29.3 | 17.3    T 48: K 65536 32.0 | 27.0; 36.9 | 36.4
-// and 32 lanes while 16 lanes leave SIMDs idle (T 30, K 3001: 5.9 with 16
-// lanes, 6.5 with 32; T 77, K 3001: 8.8 and 8.2).
-// The costs above search cells (circles, or a two-valued costmap's bitmap) at
-// every step, which the lanes share.  Where there are none to search a step is
-// short and the lines lie further out.  An iteration, grouped or one-lane over
-// time-parallel, quadratic cost; a spline with a costmap of many values:
-//   K 64: T 1 7.0/8.1; 7.7/8.9, T 4 7.5/8.2; 8.0/9.0, T 16 10.2/9.1; 10.5/8.8
-//   K 8192: T 8 10.7/11.1; 11.5/11.8, T 16 14.1/12.8; 15.1/13.4
-//   K 16384: T 16 15.7/16.2, T 24 0.95 of it; K 32768: T 24 0.99, 0.98 of it
-//   K 36864: T 128 time-parallel 1.11 of it; 0.87   K 57344: T 100 1.06; 0.95
-//   K 65536: T 48 1.09; 1.03, T 100 1.12; 1.08, T 160 0.80; 0.77
-//   K 98304: T 48 1.21; 1.20, T 100 1.01; 1.00, T 256 1.04; 1.09
-// and with cells K 98304: T 48 1.03, T 64 0.96, K 8192: T 1 11.1/11.7, T 8 0.93.
-int default_scan_lanes(const Instance& I) {
-  if (I.hidden || I.grad || (I.cfg.flags & (MPPI_F_ROLLOUT_LANE | MPPI_F_ROLLOUT_QUAD))) return 0;
-  const int lanes = I.K <= 1024 || (I.K <= 4096 && I.T > 64) ? 32 : 16;
-  if (!rollout_scan_supported(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, I.T, lanes)) return 0;
-  constexpr int kNever = 1 << 30;
-  const bool cells = uses_circles(I.cfg.cost) ? I.dp.ncirc > 0
-                                              : I.cfg.cost == MPPI_COST_PATH_COSTMAP &&
-                                                    I.dp.map_bits4 >= 0;
-  int min_steps;
-  if (cells)
-    min_steps = I.K > 65536   ? 64
-                : I.K > 32768 ? 48
-                : I.K > 16384 ? 24
-                : I.K > 8192  ? 16
-                : I.K > 4096  ? 6
-                              : 1;
-  else if (I.K <= 32768)
-    min_steps = I.K > 8192 ? 24 : 12;
-  else if (!uses_spline(I.cfg.cost))
-    min_steps = kNever;
-  else
-    min_steps = I.K > 65536 ? kNever : I.K > 57344 ? 160 : 48;
-  return I.T >= min_steps ? lanes : 0;
-}
-
-// Threads per workgroup of the fused rollout of a context whose launch shapes
-// nobody has chosen: with 64 the dispatcher puts waves on SIMDs that hold one
-// while others are empty, with 256 every CU's four SIMDs get one each.  One
-// iteration, 64 | 256 threads, us: quadrotor K 65536 T 200 271 | 236, K 32768
-// T 200 196 | 190, K 10007 T 200 147 | 145; double integrator K 65536 T 200
-// 99 | 97; bicycle (one lane) K 65536 T 30 47 | 42.  Below, for the shorter
-// steps, one wave per CU is the better: double integrator K 16384 T 100 17.4
-// and 19.1 for the rollout.
-int default_rollout_block(const mppi_ctx* c) {
-  const Instance& I = c->one();
-  if (I.lanes == 1 && (I.K >= 32768 || I.cfg.dynamics == MPPI_DYN_QUADROTOR)) return 256;
-  return c->tune.rollout_block;
-}
-
 // next: also draw the next iteration's noise (rollout_draws_noise only).
 hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
   const Instance& I = c->one();
@@ -1273,18 +1274,18 @@ hipError_t phase_rollout(mppi_ctx* c, bool next = false) {
                                 c->tune.rollout_block, c->tune.cost_waves);
   NoiseJob job{};
   if (next) job = next_noise_job(c);
-  const int scan = c->tuned ? (c->tune.rollout_form == MPPI_ROLLOUT_SCAN
-                                   ? c->tune.lanes_per_sample : 0)
-                            : default_scan_lanes(I);
+  const bool own = c->tune.lanes_per_sample == 0;  // the library's choice
+  const int scan = own                                          ? default_scan_lanes(I)
+                   : c->tune.rollout_form == MPPI_ROLLOUT_SCAN ? c->tune.lanes_per_sample
+                                                               : 0;
   if (scan)
     return launch_rollout_scan(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.dp, I.x0,
                                I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
-                               c->work(), c->tuned ? c->tune.rollout_block : 256,
-                               next ? &job : nullptr, scan);
+                               c->work(), own ? 256 : c->tune.rollout_block, next ? &job : nullptr,
+                               scan);
   return launch_rollout(I.cfg.dynamics, I.cfg.integrator, I.cfg.cost, accurate, I.lanes, I.dp, I.x0,
                         I.u, I.eps(), I.L.ldk, I.K, I.T, I.S, count ? I.crashes : nullptr,
-                        c->work(), c->tuned ? c->tune.rollout_block : default_rollout_block(c),
-                        next ? &job : nullptr);
+                        c->work(), c->tune.rollout_block, next ? &job : nullptr);
 }
 
 // next: the weights launch also draws the next iteration's noise into the
@@ -1505,8 +1506,10 @@ mppi_status mppi_get_tuning(const mppi_ctx* c, mppi_tuning* out) {
   return MPPI_OK;
 }
 
-mppi_status mppi_set_tuning(mppi_ctx* c, const mppi_tuning* t) {
-  if (!c || !t) return fail(MPPI_EINVAL, "ctx and t must not be NULL");
+mppi_status mppi_set_tuning(mppi_ctx* c, const mppi_tuning* want) {
+  if (!c || !want) return fail(MPPI_EINVAL, "ctx and t must not be NULL");
+  mppi_tuning shape_of = *want;
+  const mppi_tuning* t = &shape_of;
   c->ahead = false;  // the word or a noise buffer may change
   auto shape = [](int v) { return v == 64 || v == 128 || v == 256; };
   if (!shape(t->rollout_block) || !shape(t->batch_tile))
@@ -1549,6 +1552,13 @@ mppi_status mppi_set_tuning(mppi_ctx* c, const mppi_tuning* t) {
     return fail(MPPI_EUNSUPPORTED, "the chunked update exists for single contexts (no gradient "
                 "mode)");
   Instance& I = c->inst[0];
+  // the library's choice: where it is the time-parallel form, in which no other is
+  // named; the split form then takes the lanes of the fused one
+  if (t->lanes_per_sample == 0 && t->rollout_form == MPPI_ROLLOUT_SPLIT && !c->batch &&
+      default_scan_lanes(I))
+    shape_of.lanes_per_sample = c->fused_lanes;
+  const bool own = t->lanes_per_sample == 0 && t->rollout_form == MPPI_ROLLOUT_FUSED &&
+                   !c->batch && default_scan_lanes(I);
   if (t->rollout_form == MPPI_ROLLOUT_SPLIT) {
     if (c->batch || !I.split)
       return fail(MPPI_EUNSUPPORTED, "the split rollout form exists for single contexts with "
@@ -1582,16 +1592,15 @@ mppi_status mppi_set_tuning(mppi_ctx* c, const mppi_tuning* t) {
       return fail(MPPI_EUNSUPPORTED, "4, 8 or 16 lanes per sample exist for a single bicycle "
                   "instance with RK4 only");
   } else if (t->lanes_per_sample != 1 &&
-             !(t->lanes_per_sample == 32 && t->rollout_form == MPPI_ROLLOUT_SCAN)) {
+             !(t->lanes_per_sample == 32 && t->rollout_form == MPPI_ROLLOUT_SCAN) && !own) {
     return fail(MPPI_EINVAL, "lanes_per_sample must be 1, 4, 8 or 16 (or 32 in the scan form)");
   }
   if (c->batch && t->batch_tile != c->plan.tile) {
     const mppi_status st = upload_sample_tiles(c, t->batch_tile);
     if (st != MPPI_OK) return st;
   }
-  if (!(I.hidden || I.grad)) I.lanes = t->lanes_per_sample;
+  if (!(I.hidden || I.grad) && !own) I.lanes = t->lanes_per_sample;
   c->tune = *t;
-  c->tuned = true;
   c->drop_graphs();
   return MPPI_OK;
 }

@@ -399,6 +399,75 @@ def case_default_rollout(b):
         b.L.mppi_destroy(ctx)
 
 
+def case_partial_tuning(b):
+    """Setting one launch shape leaves the others, the rollout's form among them;
+    setting what was reported changes nothing."""
+    def get(ctx):
+        t = b.abi.Tuning()
+        b.ok(b.L.mppi_get_tuning(ctx, C.byref(t)))
+        return t
+
+    def put(ctx, **shape):
+        t = get(ctx)
+        for k, v in shape.items():
+            setattr(t, k, v)
+        return b.L.mppi_set_tuning(ctx, C.byref(t))
+
+    ctx = b.bicycle(8192, 100, "circles")
+    assert get(ctx).rollout_form == 0 and get(ctx).lanes_per_sample == 0
+    default = b.rollout_kernel(ctx)
+    assert default == ("scan", 16, 256)
+    for shape in ({}, {"noise_calls": 2}, {"update_form": 0}, {"rollout_block": 128},
+                  {"cost_waves": 4}, {"adjoint_tiles": 3}):
+        b.ok(put(ctx, **shape))
+        assert b.rollout_kernel(ctx) == default, shape
+    assert get(ctx).noise_calls == 2 and get(ctx).update_form == 0
+    b.ok(put(ctx, lanes_per_sample=4, rollout_block=64))
+    assert b.rollout_kernel(ctx) == ("group", 4, 64)
+    b.ok(put(ctx))
+    assert b.rollout_kernel(ctx) == ("group", 4, 64)
+    b.ok(put(ctx, rollout_form=2, lanes_per_sample=32, rollout_block=128))
+    assert b.rollout_kernel(ctx) == ("scan", 32, 128)
+    assert put(ctx, lanes_per_sample=0) == -1  # the scan form names its lanes
+    b.ok(put(ctx, rollout_form=0, lanes_per_sample=0))
+    assert b.rollout_kernel(ctx) == default
+    b.ok(put(ctx, rollout_form=1))  # the split form with the fused form's lanes
+    assert get(ctx).lanes_per_sample == 4
+    b.L.mppi_destroy(ctx)
+    for K, cost, kernel in ((40000, "quadratic", ("lane", 1, 256)),
+                            (20000, "quadratic", ("group", 4, 64))):
+        ctx = b.bicycle(K, 20, cost)
+        assert b.rollout_kernel(ctx) == kernel
+        assert (get(ctx).lanes_per_sample, get(ctx).rollout_block) == kernel[1:]
+        b.ok(put(ctx, noise_calls=4))
+        assert b.rollout_kernel(ctx) == kernel
+        assert put(ctx, lanes_per_sample=0) == -1  # not the library's choice here
+        b.L.mppi_destroy(ctx)
+    for flag, kernel in ((b.abi.F_ROLLOUT_LANE, ("lane", 1, 64)), (b.abi.F_ROLLOUT_QUAD, ("group", 4, 64))):
+        ctx = b.bicycle(500, 60, "circles", flag)
+        assert b.rollout_kernel(ctx) == kernel and get(ctx).lanes_per_sample == kernel[1]
+        assert put(ctx, lanes_per_sample=0) == -1
+        b.L.mppi_destroy(ctx)
+    for make in (lambda: b.context(b.hip.model_stream(0)), lambda: b.context(b.hip.model_stream(0), batch=2),
+                 lambda: b.context(b.hip.model_stream(0), hidden=64)):
+        ctx = make()
+        assert put(ctx, lanes_per_sample=0) < 0
+        b.ok(put(ctx))
+        b.L.mppi_destroy(ctx)
+
+
+def case_autotune(b):
+    """A context created with the library's choice can be tuned; the result names
+    its shapes."""
+    ctx = b.bicycle(2000, 60, "circles")
+    report = C.create_string_buffer(1 << 16)
+    b.ok(b.L.mppi_autotune(ctx, 1, report, len(report)))
+    t = b.abi.Tuning()
+    b.ok(b.L.mppi_get_tuning(ctx, C.byref(t)))
+    assert t.lanes_per_sample > 0 and b"form=2" in report.value and b"form=1" in report.value
+    b.ok(b.L.mppi_rollout(ctx))
+
+
 CASES = {n[5:]: f for n, f in list(globals().items()) if n.startswith("case_")}
 
 
