@@ -159,7 +159,9 @@ __global__ __launch_bounds__(kWave * split_launch_waves(SW)) void rollout_tile_s
   using tile_t = std::conditional_t<BF, mlp::bf4, f4>;  // BF: rounded by the wave that formed it
   __shared__ tile_t xh[MT][kWave];           // h1 tiles
   __shared__ tile_t xg[BF ? MT : 1][kWave];  // BF: h2 tiles
-  __shared__ float xo[BF ? 1 : MT][kTile][kOut];  // output partials 0..4 per K-tile
+  // output partials 0..4 per K-tile, read four at a time
+  __shared__ alignas(sizeof(f4)) float xo[BF ? 1 : MT][kTile][kOut];
+  static_assert(sizeof(float) * kOut % sizeof(f4) == 0, "a sample's row starts aligned");
   __shared__ float xq[kTile][8];             // the bicycle's increment
   extern __shared__ float4 lds[];
   const float* lds_u = stage_rollout_lds<Cost>(p, u, T * M, lds);
