@@ -273,7 +273,7 @@ __device__ __forceinline__ float track_dq(float a, float d, float gq) {
 }
 
 // d = (df/dx) xd: the bicycle derivative's tangent along xd at x (control
-// held), the forward-mode counterpart of bicycle_vjp.
+// held), the forward-mode counterpart of a stage in rk4_vjp.
 template <bool FAST>
 __device__ __forceinline__ void bicycle_jvp(const float* x, const float* xd, float inv_l,
                                             float* d) {
@@ -1462,8 +1462,12 @@ __global__ __launch_bounds__(kWave * sweep_launch_waves(SW), MT == 2 ? 4 : 2)
   const int m3 = (n & 3) == 0 ? n / 4 : (n & 3) == 1 ? 4 : 15;
   const int m1 = (n & 3) == 0 ? n / 4 : 3 + (n & 3);
   // The operand slices of the rebuild and of the reverse pass are fetched anew
-  // for every unit (L1 / L2), so that the registers hold one set at a time: two
-  // workgroups of eight waves need at most 128 registers a lane.
+  // for every unit (L1 / L2), so that the registers hold one set at a time.  A
+  // workgroup of ten waves (H = 64, SW = 4) has 168 registers a lane (2 spilled).
+  // H = 32 is held to 128, so that two workgroups of six waves share a CU, and
+  // spills 9 (BF) to 20: with 168 nothing is spilled and two tiles per CU take 256
+  // us instead of 264, but one workgroup fits, and three and four tiles per CU take
+  // 465 and 491 instead of 375 and 398 (T = 100, every sample weighted).
   auto fresh = [](const auto* ptr) {
     asm volatile("" : "+s"(ptr));
     return ptr;

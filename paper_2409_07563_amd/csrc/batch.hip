@@ -26,8 +26,8 @@ static_assert(sizeof(WorkItem) == sizeof(int2) && alignof(WorkItem) <= alignof(i
 // consecutive samples (16-byte stores) and a wave every fourth call of its
 // slice; smaller tiles: one thread per sample.
 // VALU-bound.  With one thread per sample running all its calls a batch of a
-// few thousand samples left most SIMDs idle: 12 instances with 20 000 samples
-// in all took 33 us, with the slices 7; 256 instances with 1.6 M samples 347
+// few thousand samples left most SIMDs idle: 12 instances with 8904 samples
+// in all took 33 us, with the slices 7; 256 instances with 1.56 M samples 347
 // and 344.
 __global__ __launch_bounds__(kBatchMaxTile) void batch_noise_kernel(
     const BatchInst* __restrict__ insts, const int2* __restrict__ tiles) {

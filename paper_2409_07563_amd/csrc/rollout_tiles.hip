@@ -502,9 +502,9 @@ namespace {
 // is short.  With H = 32 two or three one-wave tiles share a SIMD at little cost,
 // so all tiles or none.  An iteration, T = 100, us, split | one wave:
 //   H = 64, 1 to 4 tiles per CU (K 4096 each): 90 145 215 294 | 250 256 260 263;
-//     5, 6, 8: 388 437 578 | 469 470 475, a round and the rest split 342 396 475
+//     5, 6, 8: 388 437 578 | 469 470 475, a round and the rest split 354 403 470
 //   H = 64, bfloat16: 66 100 143 203 | 126 132 137 137; 5, 6, 8: 252 283 362 |
-//     234 235 238, a round and the rest split 203 236 238 (T = 30, 6: 83 and 87)
+//     234 235 238, a round and the rest split 208 236 237 (T = 30, 6: 83 and 87)
 //   H = 32, 1 to 12: 69 100 132 144 194 229 260 292 323 351 378 409 |
 //     135 139 144 144 231 231 233 235 330 332 335 336
 //   H = 32, bfloat16: 61 78 97 107 146 167 188 208 230 250 271 291 |
